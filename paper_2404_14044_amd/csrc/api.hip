@@ -334,7 +334,7 @@ static hp_status make_ctx(const hp_table *tab, const hp_camera *cams, int32_t n_
     c.K = p->K;
     c.S = p->n_samples;
     c.M = p->m_cap;
-    c.chunk = p->search_chunk > 0 ? p->search_chunk : 4;
+    c.chunk = p->search_chunk;
     c.band = p->search_band > 0 ? p->search_band : hp::BAND_RAYS;
     c.window = p->window_shape;
     c.blocks = p->search_blocks;

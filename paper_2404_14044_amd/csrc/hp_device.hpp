@@ -164,6 +164,17 @@ __device__ __forceinline__ void load_nbr4(const int32_t *ki, const float *kd, in
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
+// The lane number as the compiler cannot see through: what a phase of a long
+// kernel derives from it (addresses, masks) is computed where the phase begins
+// instead of being hoisted out of the kernel's outer loops, where it would
+// hold registers through every other phase and be spilled to scratch memory.
+__device__ __forceinline__ int phase_lane_id()
+{
+    int l = __lane_id();
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
 // Orders this wave's LDS accesses.  A wave's LDS operations complete in
 // program order, so a compiler barrier is enough for its lanes to see each
 // other's writes; no workgroup barrier, as several independent waves may
@@ -215,7 +226,12 @@ __device__ __forceinline__ void kswap(uint64_t &a, uint64_t &b)
     b = f64_key(__builtin_fmax(x, y));
 }
 
-__device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
+// (the builtin takes the comparison's lane mask as it is; __ballot makes an
+// integer of it first, two vector instructions more)
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+
+// whether this lane's bit of a wave-uniform lane mask is set
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 __device__ __forceinline__ int popc64(uint64_t m) { return __popcll(m); }
 

@@ -1,7 +1,7 @@
-// Per-ray hashed-point search (Sec. 3.2) and adaptive primary-surface sampling
-// (Sec. 3.3, Eq. 4, Eq. 5), one wave per ray.  Shared by the search + sampling
-// kernels (also run by the backward pass to recompute its samples), the K-NP
-// kernel and the fused search + render kernel.
+// Hashed-point search (Sec. 3.2) and adaptive primary-surface sampling
+// (Sec. 3.3, Eq. 4, Eq. 5), one wave for up to four neighbouring rays.  Shared
+// by the search + sampling kernels (also run by the backward pass to recompute
+// its samples), the K-NP kernel and the fused search + render kernel.
 //
 // Search.  A neighbour of the ray is a point within rho(t) of it at its own
 // parameter t in [t_near, t_far].  Such a point projects at most
@@ -15,30 +15,34 @@
 //      bounds t and thus the window radius delta(t) (two rounds, each over the
 //      cells of the previous radius; four lanes per ray do this for up to
 //      sixteen rays at once, ray_setup);
-//   2. the wave visits the buckets of that disc, and inside a bucket at distance D from
-//      the pixel centre only needs points with t <= f r L^2 / D + r |w|, i.e.
-//      z <= (f r L^2 / D + 2 r |w|) / L (fixed-radius branch of rho); buckets
-//      are ordered by z, so a bucket whose first point is deeper is skipped.
+//   2. inside a bucket at distance D from the pixel centre only points with
+//      t <= f r L^2 / D + r |w|, i.e. z <= (f r L^2 / D + 2 r |w|) / L, can be
+//      neighbours (fixed-radius branch of rho); buckets are ordered by z, so a
+//      bucket whose first point is deeper is skipped.
 // Every bound is widened by relative margins far above binary32 rounding; the
 // exact predicate decides.
 //
-// Lanes first sweep the window buckets (one bucket per lane), compact the
-// non-empty survivors into an LDS list, then sweep the points of the listed
-// buckets (one point per lane, its bucket found by a prefix maximum over the
-// bucket heads), apply the exact predicate and append the keys
-// (t bits << 32 | point index) of passing points to a pending buffer.  Every
-// 64 pending keys are sorted across the wave and merged into a running
-// ascending top-64, whose largest key then filters later appends.
+// Up to four rays of one image row are searched together (search_group): their
+// windows overlap almost entirely, so the buckets' headers, the points' loads
+// and the bookkeeping that deals points to lanes are paid once, and only the
+// exact predicate is evaluated per ray.  Keys (t bits << 32 | point index) of
+// passing points go to the ray's pending buffer, which is cut back to the
+// smallest 64 to 128 when it fills (keep_smallest); it is never sorted there.
 //
-// Sampling.  Candidates are the neighbours in (t, index) order.  The K
-// nearest neighbours of candidate j within R_j = rho(t_j) lie in the window
-// |t_i - t_j| <= R_j of the sorted list (distance >= |t_i - t_j| up to
-// rounding), found by binary search.  Sixteen candidates are served at once,
-// four lanes each: the lanes split the window, keep sorted register lists of
-// (dist^2 bits << 32 | index) and merge them across the quad.  The wave then
-// walks those candidates in order accumulating the transmittance of Eq. 5 and
-// stops once no later candidate can pass eps_w (alpha <= gamma, so
-// w_j <= gamma T), which usually happens within the first sixteen.
+// Sampling (walk_batch).  Candidates are the neighbours in (t, index) order,
+// sorted for four rays at once, one row of 16 lanes each; every lane serves
+// one candidate.  The K nearest neighbours of candidate j within R_j =
+// rho(t_j) lie in the window |t_i - t_j| <= R_j of the sorted list (distance
+// >= |t_i - t_j| up to rounding).  The row then walks its candidates in order
+// accumulating the transmittance of Eq. 5 and stops once no later candidate
+// can pass eps_w (alpha <= gamma, so w_j <= gamma T), which usually happens
+// within the first sixteen.
+//
+// The kernels are bound by instruction issue, vector and scalar, not by
+// memory (object view, 640k rays, 1M points: 1.0 TB/s).  One ray at a time,
+// with sorted lists kept by merging and four lanes to a candidate, took 285M
+// vector and 112M scalar instructions and 0.490 ms there; this way it takes
+// 0.317 ms (room view, 762k rays, 5M points: 2.79 -> 1.35 ms).
 #pragma once
 #include "hp_device.hpp"
 
@@ -65,6 +69,30 @@ struct SearchCtx {
     int32_t window;         // HP_WINDOW_*: disc of buckets, or the square around it
 };
 
+// The kernel's argument number 0, which is the SearchCtx in every kernel that
+// searches, and the argument after it, copied anew where a phase begins (a
+// copy: read through the pointer, a field would be loaded again after every
+// store).  Bound to the arguments themselves, the compiler loads all of them when the kernel
+// starts; the search's own scalars then push them out to vector lanes, and
+// every use costs a vector instruction per word to bring them back (a scalar
+// load from the constant cache costs none).
+template <typename T>
+__device__ __forceinline__ T kernel_arg(size_t at)
+{
+    typedef const __attribute__((address_space(4))) char *ConstPtr;
+    ConstPtr p = (ConstPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const T *)(p + at);
+}
+
+__device__ __forceinline__ SearchCtx phase_ctx() { return kernel_arg<SearchCtx>(0); }
+
+template <typename T>
+__device__ __forceinline__ T phase_arg()
+{
+    return kernel_arg<T>((sizeof(SearchCtx) + alignof(T) - 1) / alignof(T) * alignof(T));
+}
+
 // One ray's geometry and search bounds, uniform across the wave that
 // searches it (computed once per ray by one lane, see ray_setup).
 struct RayGeom {
@@ -80,22 +108,92 @@ struct RayGeom {
     float Dmax;          // window radius in pixels
 };
 
-constexpr int BL_CAP = 128;
 constexpr int RS_CAP = 16;              // rays whose set-up one pass computes
 constexpr int RS_LANES = WAVE / RS_CAP;  // lanes per ray in that pass
 
-struct SearchLds {
+// Neighbouring rays searched together, at most: rays of one image row whose
+// windows overlap.  What a window costs (its buckets' headers, its points'
+// loads, the bookkeeping that deals points to lanes) is then paid once for up
+// to four rays, and only the exact predicate is evaluated for each.
+constexpr int GROUP = 4;
+
+// Keys a ray holds after a sweep step, at most (and 64 more during one).  Four
+// rays share the LDS of a wave: 128 each are what the walk can sort without
+// being told which 64 it needs, and 64 do for K-NP, which keeps few.  One ray
+// alone, the multi-surface sampler's, has room for all its neighbours in most
+// cases.
+constexpr int HELD_WALK = 2 * WAVE;
+constexpr int HELD_KNP = WAVE;
+constexpr int HELD_SLAB = 8 * WAVE;
+constexpr int BL_CAP = 3 * 64;  // listed buckets: a wave's worth, and two cells more
+
+// One wave's LDS while it searches G rays, holding HELD keys of each.
+template <int G, int HELD>
+struct SearchScratch {
+    uint64_t pend[G][HELD + WAVE];  // keys of the neighbours found so far
+    int2 bl[BL_CAP];             // listed buckets: key, offset from the window's corner (16 bits each)
+    int2 cl[WAVE];               // listed depth cells: first bucket in the window, width and prefix (16 bits each)
+    int32_t head[WAVE];          // (indexed by flat point offset within a sweep step)
+};
+
+// The rays a wave holds between search and walk.
+struct RaySlot {
+    int32_t ray;    // row of the outputs
+    int32_t rs;     // set-up record
+    int32_t n;      // keys held
+    int32_t count;  // neighbours (any number above those asked for where there are more)
+};
+
+// The lists of the rays one walk serves (walk_batch): GROUP rows of 64
+// points in (t, index) order, WALK_PAD empty entries before, between and
+// after them, so that a batch of WALK_PAD entries that reaches past a list's
+// ends needs no test.
+constexpr int WALK_PAD = 8;
+constexpr int WALK_STRIDE = WAVE + WALK_PAD;
+
+struct WalkLists {
+    float4 p[WALK_PAD + GROUP * WALK_STRIDE];
+};
+
+// Search, then walk: the two never hold data at the same time (the walk reads
+// the keys into registers before it writes its lists).
+struct WalkLds {
     RayGeom rs[RS_CAP];
-    int32_t bl_start[BL_CAP];
-    int32_t bl_cnt[BL_CAP];
-    int32_t bl_pre[WAVE];  // (indexed by flat point offset within a sweep step)
-    float bl_zmax[BL_CAP];
-    uint64_t pend[2 * WAVE];
+    RaySlot slot[GROUP];
+    alignas(16) unsigned char mem[sizeof(SearchScratch<GROUP, HELD_WALK>) > sizeof(WalkLists) ? sizeof(SearchScratch<GROUP, HELD_WALK>)
+                                                                                   : sizeof(WalkLists)];
+
+    __device__ __forceinline__ SearchScratch<GROUP, HELD_WALK> &search()
+    {
+        return *reinterpret_cast<SearchScratch<GROUP, HELD_WALK> *>(mem);
+    }
+    __device__ __forceinline__ WalkLists &lists() { return *reinterpret_cast<WalkLists *>(mem); }
+};
+// (LDS is granted in pieces of 1,280 B: eight of them let 16 one-wave
+// workgroups share a CU's 160 KB)
+static_assert(sizeof(WalkLds) <= 10240, "walk LDS above 10240 B costs occupancy");
+
+struct KnpLds {
+    RayGeom rs[RS_CAP];
+    RaySlot slot[GROUP];
+    SearchScratch<GROUP, HELD_KNP> s;
+};
+static_assert(sizeof(KnpLds) <= 7680, "K-NP LDS above 7680 B costs occupancy");
+
+// The multi-surface sampler: one ray's neighbours, and a slab of 64 of them at
+// a time with their points.
+struct SlabList {
     float4 nb_p[WAVE];
     float nb_t[WAVE];
 };
-// 32 one-wave workgroups (8 waves per SIMD) share a CU's 160 KB of LDS
-static_assert(sizeof(SearchLds) <= 5120, "search LDS above 5120 B halves occupancy");
+
+struct SlabLds {
+    RayGeom rs[RS_CAP];
+    RaySlot slot[1];
+    SearchScratch<1, HELD_SLAB> s;
+    SlabList list;
+};
+static_assert(sizeof(SlabLds) <= 10240, "slab LDS above 10240 B costs occupancy");
 
 // Rays per XCD band: two image rows of an 800-pixel-wide view (object view
 // 0.568 ms with bands of 12,800 rays, 0.545 with 3,200, 0.532 with 1,600,
@@ -109,6 +207,19 @@ constexpr int64_t BAND_RAYS = 1600;
 // 0.631 ms, 65,536 0.56 ms; room view 4.04 vs 3.69 ms; one workgroup per
 // chunk 0.58 / 3.91 ms).
 constexpr int64_t DEFAULT_SEARCH_BLOCKS = 65536;
+
+// Rays per work chunk where the caller names none.  Neighbouring rays are
+// searched together, so a chunk of four or more is the cheapest by ray; a
+// launch of few rays leaves most of the GPU idle that way and is better split
+// further (us by rays per chunk, 1 / 2 / 4 / 8, object cloud of 758k points:
+// 2,304 rays 61 / 116 / 227 / 424; 16,384 rays 90 / 93 / 223 / 362; 65,536 rays
+// 146 / 110 / 126 / 173; 640,000 rays 690 / 493 / 414 / 403; room of 1.3M points:
+// 4,096 rays 95 / 146 / 210 / 312; 147,456 rays 626 / 510 / 338 / 297).
+// The multi-surface sampler takes its rays one at a time, each for long.
+inline int32_t default_chunk(const SearchCtx &c)
+{
+    return c.n_rays <= 6144 ? 1 : c.n_rays <= 32768 ? 2 : c.n_rays <= 262144 || c.sampler == HP_SAMPLER_MS ? 4 : 8;
+}
 
 // Grid for the banded launches: at most `cap` workgroups, a multiple of 8.
 inline int64_t banded_grid(const SearchCtx &c, int64_t cap)
@@ -379,14 +490,15 @@ __device__ __forceinline__ float ray_first_zmin(const SearchCtx &c, int64_t ray,
     return group_cells_zmin(c, V, local % V.W + V.g, local / V.W + V.g, first_round_h(V), sub);
 }
 
-// (zmin1: the first round's minimum depth, ray_first_zmin, already taken)
-__device__ __forceinline__ RayGeom ray_setup(const SearchCtx &c, int64_t ray, int sub, float zmin1)
+// (zmin1: the first round's minimum depth, ray_first_zmin, already taken; u: the ray's pixel column)
+__device__ __forceinline__ RayGeom ray_setup(const SearchCtx &c, int64_t ray, int sub, float zmin1, int &u)
 {
     RayGeom g;
     const int vi = ray_view(c, ray);
     const ViewK &V = c.views[vi];
     const int local = (int)(ray - V.ray_base);
-    const int u = local % V.W, v = local / V.W;
+    const int v = local / V.W;
+    u = local % V.W;
     float a, b, L;
     ray_dir(V, u, v, g.dx, g.dy, g.dz, a, b, L);
     g.vi = vi;
@@ -490,19 +602,23 @@ __device__ __forceinline__ RayGeom load_ray(const RayGeom &src)
 // The first depth-cell round goes first: a ray whose view-wide window holds
 // no point (most rays of a view that an object does not fill) is finished
 // there by empty(ray), called on one lane per such ray, and neither gets the
-// rest of the set-up nor a pass of the wave.
-template <typename Body, typename Empty>
-__device__ __forceinline__ void for_each_ray_banded(const SearchCtx &c, RayGeom *rs, Body body,
-                                                    Empty empty)
+// rest of the set-up nor a pass of the wave.  groups(n, ray, first, last) is then
+// called for the others, up to MAXG rays of one image row with consecutive
+// pixels at a time: their number, the first one's number (rays numbered from
+// the launch's first one, which is their row in the outputs) and its record
+// (the others' follow), and whether this pass ends with them.
+template <int MAXG, typename Groups, typename Empty>
+__device__ __forceinline__ void for_each_group_banded(RayGeom *rs, Groups groups, Empty empty)
 {
-    const int l = lane_id();
+    const SearchCtx cl = phase_ctx();
     // (chunk, band and slot numbers in 32 bits: a launch has fewer than 2^31
     // rays, so every chunk number below fits an unsigned 32-bit integer, and
     // 64-bit ones held scalar registers that the body then spilled)
-    const uint32_t n_chunks = (uint32_t)((c.n_rays + c.chunk - 1) / c.chunk);
+    const uint32_t n_chunks = (uint32_t)((cl.n_rays + cl.chunk - 1) / cl.chunk);
+    const uint32_t chunk = (uint32_t)cl.chunk, n_rays = (uint32_t)cl.n_rays;
     // chunks per band (fewer when the launch has fewer than eight full bands,
     // so that every XCD gets a share)
-    uint32_t band = (uint32_t)(((int64_t)c.band + c.chunk - 1) / c.chunk);
+    uint32_t band = (uint32_t)(((int64_t)cl.band + cl.chunk - 1) / cl.chunk);
     if ((uint64_t)band * 8 > n_chunks) band = (n_chunks + 7) / 8 > 0 ? (n_chunks + 7) / 8 : 1;
     const uint32_t xcd = blockIdx.x & 7;
     const uint32_t slot = blockIdx.x >> 3, n_slots = gridDim.x >> 3;
@@ -515,11 +631,13 @@ __device__ __forceinline__ void for_each_ray_banded(const SearchCtx &c, RayGeom 
         if (li >= my_chunks) return;
         const uint32_t ch = (xcd + 8 * (li / band)) * band + li % band;
         if (ch >= n_chunks) return;
-        r0 = ch * (uint32_t)c.chunk;
-        n = (int)min((int64_t)c.chunk, c.n_rays - (int64_t)r0);
+        r0 = ch * chunk;
+        n = (int)min(chunk, n_rays - r0);
     };
     // four chunks per set-up pass (the chunks themselves stay small, for balance)
     for (uint32_t li = slot; li < my_chunks; li += 4 * n_slots) {
+        const SearchCtx c = phase_ctx();
+        const int l = phase_lane_id();
         uint32_t ra, rb, rc, rd;
         int na, nb, nc, nd;
         chunk_rays(li, ra, na);
@@ -529,7 +647,7 @@ __device__ __forceinline__ void for_each_ray_banded(const SearchCtx &c, RayGeom 
         const int nab = na + nb, nabc = nab + nc, ntot = nabc + nd;
         auto ray_at = [&](int i) -> int64_t {
             const uint32_t r = i < na ? ra + i : i < nab ? rb + (i - na) : i < nabc ? rc + (i - nab) : rd + (i - nabc);
-            return c.ray0 + (int64_t)r;
+            return (int64_t)r;
         };
         for (int s0 = 0; s0 < ntot; s0 += RS_CAP) {
             const int n = min(RS_CAP, ntot - s0);
@@ -537,263 +655,439 @@ __device__ __forceinline__ void for_each_ray_banded(const SearchCtx &c, RayGeom 
             // repeat its last ray)
             const int k = l / RS_LANES, sub = l % RS_LANES;
             const int64_t rk = ray_at(s0 + (k < n ? k : n - 1));
-            const float z1 = ray_first_zmin(c, rk, sub);
+            const float z1 = ray_first_zmin(c, c.ray0 + rk, sub);
             const bool lead = sub == 0 && k < n;
             const uint64_t near = ballot(lead && z1 < __builtin_inff());  // bit RS_LANES k
             if (lead && !(z1 < __builtin_inff())) empty(rk);
             if (near == 0) continue;
             lds_sync();
-            const RayGeom gk = ray_setup(c, rk, sub, z1);
+            int u;
+            const RayGeom gk = ray_setup(c, c.ray0 + rk, sub, z1, u);
             if (lead) rs[k] = gk;
             lds_sync();
-            for (int i = 0; i < n; ++i)
-                if ((near >> (RS_LANES * i)) & 1ull) body(ray_at(s0 + i), load_ray(rs[i]));
+            // rays whose left neighbour is the one before them in this pass
+            const int prev = __shfl_up((int)rk, RS_LANES, WAVE);
+            const uint64_t joined = near & (near << RS_LANES) & ballot((int)rk == prev + 1) &
+                                    ballot(u > 0);
+            for (uint64_t todo = near; todo != 0;) {
+                const int i = __builtin_ctzll(todo) / RS_LANES;
+                int m = 1;
+                while (m < MAXG && ((joined >> (RS_LANES * (i + m))) & 1ull)) ++m;
+                todo &= ~(((1ull << (RS_LANES * m)) - 1ull) << (RS_LANES * i));
+                groups(m, (int)ray_at(s0 + i), i, todo == 0);
+            }
         }
     }
 }
 
-// Search one ray.  Returns, in `top` (one key per lane, ascending), the
-// 64 smallest (t, index) keys of the ray's neighbours (missing = ~0), and
-// the total neighbour count; with `lo`, only the keys >= lo count (the
+// Keep the `want` smallest of the n > want pending keys (n <= CAP) and at
+// most `spare` others, in any order, at the front of `pend`; n becomes their
+// number.  Returns an upper half that no dropped key's is below and no kept
+// key's above.  The cut is found as quickselect finds it, on the keys' upper
+// halves: one of the keys still in question is the next pivot, and a ballot
+// and a population count per register of keys tell its rank (two or three
+// steps where `spare` is 64; bisection of the range of values takes fifteen,
+// and sorting every 64 keys that arrive and merging them into a sorted list
+// took four times the vector instructions of that).  Equal upper halves at
+// the cut are told apart by bisection on the lower halves.
+template <int CAP>
+__device__ __forceinline__ uint32_t keep_smallest(uint64_t *pend, int &n, int want, int spare)
+{
+    constexpr int NR = (CAP + WAVE - 1) / WAVE;
+    const int l = phase_lane_id();
+    lds_sync();
+    // (upper halves are bits of non-negative binary32 values, infinity
+    // included; the padding lies above all of them)
+    int hi[NR];
+    uint32_t lo[NR];
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+        const uint64_t key = WAVE * k + l < n ? pend[WAVE * k + l] : 0x7fffffffffffffffull;
+        hi[k] = (int)(key >> 32);
+        lo[k] = (uint32_t)key;
+    }
+    lds_sync();
+    // fewer than `want` keys at or below a, s >= `want` at or below b
+    int a = -1, b = 0x7ffffffe, s = n;
+    while (s > want + spare) {
+        int pivot = -1;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const uint64_t in = ballot(hi[k] > a) & ballot(hi[k] < b);
+            if (in) pivot = readlane_i32(hi[k], __builtin_ctzll(in));
+        }
+        if (pivot < 0) break;  // all that are left equal b
+        int t = 0;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) t += popc64(ballot(hi[k] <= pivot));
+        if (t >= want) {
+            b = pivot;
+            s = t;
+        } else {
+            a = pivot;
+        }
+    }
+    uint32_t cut = ~0u;  // lower halves kept at upper half b
+    if (s > want + spare) {
+        int need = want;  // of the keys at b
+#pragma unroll
+        for (int k = 0; k < NR; ++k) need -= popc64(ballot(hi[k] < b));
+        auto tied = [&](uint32_t v) {
+            int t = 0;
+#pragma unroll
+            for (int k = 0; k < NR; ++k) t += popc64(ballot(hi[k] == b) & ballot(lo[k] <= v));
+            return t;
+        };
+        uint32_t c = 0u;
+        if (tied(0u) >= need) {
+            cut = 0u;
+        } else {
+            while (cut - c > 1u) {
+                const uint32_t mid = c + ((cut - c) >> 1);
+                if (tied(mid) >= need) cut = mid;
+                else c = mid;
+            }
+        }
+    }
+    int at = 0;
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+        const uint64_t m = ballot(hi[k] < b) | (ballot(hi[k] == b) & ballot(lo[k] <= cut));
+        if (in_mask(m)) pend[at + rank_below(m)] = ((uint64_t)(uint32_t)hi[k] << 32) | lo[k];
+        at += popc64(m);
+    }
+    n = at;
+    lds_sync();
+    return (uint32_t)b;
+}
+
+// Windows of up to ROW_WIN rows that hold up to ROW_POINTS points are searched
+// as runs of consecutive table slots, one lane per run.
+constexpr int ROW_WIN = 15;
+constexpr int ROW_POINTS = 640;
+
+__device__ __forceinline__ float quad_max_f32(float v)
+{
+    v = __builtin_fmaxf(v, __uint_as_float(xor_lane_u32<1>(__float_as_uint(v))));
+    return __builtin_fmaxf(v, __uint_as_float(xor_lane_u32<2>(__float_as_uint(v))));
+}
+
+__device__ __forceinline__ float quad_min_f32(float v) { return -quad_max_f32(-v); }
+
+// Search the ng rays (ng <= G) of slots s0 .. s0 + ng - 1: neighbours in one
+// image row, their records in the slots.  Leaves in each ray's row of
+// sh.pend its `want` <= 64 smallest (t, index) keys (or all) and perhaps a few
+// more, in no order, at most `most` <= HELD of them, and in its slot their
+// number and the number of neighbours (any number above `want` where
+// there are more); with `lo`, only the keys >= lo count (the
 // multi-surface sampler walks a ray's neighbours 64 at a time this way).
 // BY_E2 orders the kept neighbours by (squared distance to the ray, index)
 // instead of (t, index): the K nearest points to the ray (K-NP, Eq. 1).
-template <bool BY_E2 = false>
-__device__ __forceinline__ void search_neighbours(const SearchCtx &c, const RayGeom &g,
-                                                  SearchLds &sh, uint64_t &top, int &count,
-                                                  uint64_t lo = 0)
+//
+// The rays' windows are searched as one, under bounds that hold for each of
+// them, and every point met is tested against each ray.  Three ways to the
+// points, chosen by what the window holds; the kept keys are the same:
+//  - runs: the buckets of a window row that are consecutive keys (the whole
+//    row in a row-major table, its part in each tile of a tiled one) hold
+//    consecutive slots, bounded by two offsets.  Small windows of few points
+//    take the runs' points flattened across the lanes, with no look at the
+//    buckets (no bucket is skipped for its depth: testing its points costs
+//    less than looking at it);
+//  - buckets: elsewhere the buckets of the 8x8-bucket cells that reach into
+//    the window are probed and those that may hold a neighbour listed; they
+//    are taken 64 at a time, one per lane, and every lane walks its bucket's
+//    points from the nearest on.  Buckets are ordered by depth, so the first
+//    points of all of them are the front of what the rays meet: once more
+//    than 64 neighbours of each ray are known, points too deep to be among
+//    the 64 nearest are not visited any more, nor buckets behind them;
+//  - what few lanes are left with, the tails of crowded buckets, is flattened
+//    across the wave like the runs.
+template <int G, int HELD, bool BY_E2 = false>
+__device__ __forceinline__ void search_group(const RayGeom *rs, RaySlot *slot, SearchScratch<G, HELD> &sh, int s0,
+                                             int ng, int want, int most, uint64_t lo = 0)
 {
-    const int l = lane_id();
-    const ViewK &V = c.views[g.vi];
-    const float z_lo = g.z_lo, z_hi = g.z_hi, dinf = g.dinf;
-    const float frL2 = g.frL2, two_rw = g.two_rw, inv_L = g.inv_L, Dmax = g.Dmax;
-    const int gx = g.gx, gy = g.gy, h = g.h;
+    const SearchCtx c = phase_ctx();
+    const int l = phase_lane_id();
+    // ray q of the group on lanes q, q + 4, ...
+    const RayGeom R = rs[slot[s0 + min(l & 3, ng - 1)].rs];
+    const int h = (int)uniform_f32(quad_max_f32((float)R.h));  // (half-widths are far below 2^24)
+    float dx[G], dy[G], dz[G], kappa[G], zh[G];
+    int count[G], np[G];
+    uint32_t tau[G];  // no key with a larger upper half is among the `want` smallest
+#pragma unroll
+    for (int r = 0; r < G; ++r) {
+        dx[r] = readlane_f32(R.dx, r);
+        dy[r] = readlane_f32(R.dy, r);
+        dz[r] = readlane_f32(R.dz, r);
+        kappa[r] = readlane_f32(R.kappa, r);
+        zh[r] = readlane_f32(R.z_hi, r);
+        count[r] = np[r] = 0;
+        tau[r] = ~0u;
+    }
+    const float wn_max = uniform_f32(quad_max_f32(R.wn));
+    const float z_lo = uniform_f32(quad_min_f32(R.z_lo)), dinf = uniform_f32(quad_max_f32(R.dinf));
+    float z_hi = uniform_f32(quad_max_f32(R.z_hi));
+    const float frL2 = uniform_f32(quad_max_f32(R.frL2)), two_rw = uniform_f32(quad_max_f32(R.two_rw));
+    const float inv_L = uniform_f32(quad_max_f32(R.inv_L)), Dmax = uniform_f32(quad_max_f32(R.Dmax));
+    const int gy = uniform_i32(R.gy), gx0 = readlane_i32(R.gx, 0), gx1 = gx0 + ng - 1;
+    const ViewK &V = c.views[uniform_i32(R.vi)];
     // (the square window also visits the corners beyond the proven radius)
     const bool square = c.window == HP_WINDOW_SQUARE;
-
-    top = ~0ull;
-    count = 0;
-    if (h < 0) return;  // no point anywhere near this ray
-    // the view's grid, read once (the loops below would reload it after
-    // every store they cannot prove unrelated)
     ViewK Vg;
     Vg.Wg = V.Wg;
     Vg.Hg = V.Hg;
     Vg.bucket_base = V.bucket_base;
     const int Wg = Vg.Wg, Hg = Vg.Hg, cell_base = V.cell_base, ncx = V.ncx;
 
-    uint64_t tau = ~0ull;
-    bool have_top = false;
-    int npend = 0;
-    int nbl = 0;
-
-    auto flush = [&](int take) {
-        // merge pend[0..take) (take <= 64) into top; keep the rest pending
-        lds_sync();
-        uint64_t x = (l < take) ? sh.pend[l] : ~0ull;
-        const int rem = npend - take;
-        const uint64_t y = (l < rem) ? sh.pend[take + l] : 0ull;
-        lds_sync();
-        if (l < rem) sh.pend[l] = y;
-        npend = rem;
-        // the first flush sorts straight into the (empty) top list; later ones
-        // sort descending (ascending on inverted keys) and merge
-        const uint64_t inv = have_top ? ~0ull : 0ull;
-        x = wave_sort_fast(x ^ inv) ^ inv;
-        if (have_top) top = wave_merge_low_fast(top, x);
-        else top = x;
-        have_top = true;
-        tau = readlane_u64(top, WAVE - 1);
-        lds_sync();
+    auto rho_of = [&](int r, float t) {
+        return c.rmode == HP_RADIUS_LINEAR ? search_radius(c.radius, c.inv_tref, t) : t * kappa[r];
     };
-
-    auto sweep_points = [&](int nb) {
-        // points of the listed buckets, flattened; each lane finds its bucket
-        // by a prefix maximum over the bucket heads that fall in its chunk
-        lds_sync();
-        const int c0 = (l < nb) ? sh.bl_cnt[l] : 0;
-        const int i0 = wave_incl_scan_i32(c0);
-        const int c1 = (WAVE + l < nb) ? sh.bl_cnt[WAVE + l] : 0;
-        const int i1 = wave_incl_scan_i32(c1) + readlane_i32(i0, WAVE - 1);
-        const int pre0 = i0 - c0, pre1 = i1 - c1;  // first flat index of buckets l, 64 + l
-        const int totp = readlane_i32(i1, WAVE - 1);
+    // keep the keys that fit: when more are held than a step's 64 would
+    // leave room for
+    auto cut_back = [&]() {
+#pragma unroll
+        for (int r = 0; r < G; ++r) {
+            if (np[r] <= HELD) continue;
+            // (a wide tolerance costs fewer steps, a narrow one lets fewer
+            // later keys by; short lists gain more from the second)
+            const int spare = BY_E2 ? min(HELD - want, 24) : min(HELD - want, WAVE);
+            tau[r] = keep_smallest<HELD + WAVE>(sh.pend[s0 + r], np[r], want, spare);
+            if constexpr (!BY_E2) {
+                // (as z_hi at t_far: a neighbour at parameter t is at most this deep)
+                const float tt = __uint_as_float(tau[r]);
+                zh[r] = __builtin_fminf(zh[r], ((tt + wn_max * rho_of(r, tt)) * inv_L) * 1.001f + 1e-6f);
+            }
+        }
+        if constexpr (!BY_E2) {
+            z_hi = zh[0];
+#pragma unroll
+            for (int r = 1; r < G; ++r) z_hi = r < ng ? __builtin_fmaxf(z_hi, zh[r]) : z_hi;
+            z_hi = uniform_f32(z_hi);
+        }
+    };
+    // the exact predicate on one point per lane of mask `valid`; passing keys
+    // are appended (lane masks of single comparisons, combined by the scalar
+    // unit: a mask of a compound condition costs two vector instructions more)
+    auto test_points = [&](uint64_t valid, const float4 &P) {
+        bool full = false;
+#pragma unroll
+        for (int r = 0; r < G; ++r) {
+            if (r >= ng) break;
+            const float t = ray_param(P.x, P.y, P.z, dx[r], dy[r], dz[r]);
+            const float e2 = dist2_at(P.x, P.y, P.z, dx[r], dy[r], dz[r], t);
+            const float rho = rho_of(r, t);
+            const uint32_t hi = __float_as_uint(BY_E2 ? e2 : t);
+            const uint64_t key = ((uint64_t)hi << 32) | __float_as_uint(P.w);
+            uint64_t live = valid & ballot(t >= c.t_near) & ballot(t <= c.t_far) & ballot(e2 <= rho * rho);
+            if (lo != 0) live &= ballot(key >= lo);
+            if (live == 0) continue;
+            count[r] += popc64(live);
+            const uint64_t km = live & ballot(hi <= tau[r]);
+            if (in_mask(km)) sh.pend[s0 + r][np[r] + rank_below(km)] = key;
+            np[r] += popc64(km);
+            full |= np[r] > HELD;
+        }
+        if (full) cut_back();
+    };
+    auto load_point = [&](int slot_no) {
+        float4 P = c.pts[slot_no];
+        // one 16-byte load: otherwise the compiler loads the components in
+        // two dependent pieces
+        asm volatile("" : "+v"(P.x), "+v"(P.y), "+v"(P.z), "+v"(P.w));
+        return P;
+    };
+    // the points of one run of slots per lane, at .. at + cnt - 1, flattened
+    // across the wave; with `deep`, only up to the lane's depth bound zmax
+    auto sweep_flat = [&](int at, int cnt, bool deep, float zmax) {
+        const int inc = wave_incl_scan_i32(cnt);
+        const int totp = readlane_i32(inc, WAVE - 1);
+        const int pre = inc - cnt;
+        const int shift = at - pre;  // slot of flat point p of this lane's run: p + shift
         int carry = 0;
         for (int p0 = 0; p0 < totp; p0 += WAVE) {
-            sh.bl_pre[l] = -1;
+            // run of flat point p0 + l: the last run head at or before it
             lds_sync();
-            if (l < nb && pre0 >= p0 && pre0 < p0 + WAVE) sh.bl_pre[pre0 - p0] = l;
-            if (WAVE + l < nb && pre1 >= p0 && pre1 < p0 + WAVE) sh.bl_pre[pre1 - p0] = WAVE + l;
+            sh.head[l] = -1;
             lds_sync();
-            int own = sh.bl_pre[l];
+            if (cnt > 0 && pre >= p0 && pre < p0 + WAVE) sh.head[pre - p0] = l;
+            lds_sync();
+            int own = sh.head[l];
             if (l == 0 && own < 0) own = carry;
             own = wave_prefix_max_i32(own);
             carry = readlane_i32(own, WAVE - 1);
-            const int p = p0 + l;
-            const int pa = __shfl(pre0, own & (WAVE - 1), WAVE);
-            const int pb = __shfl(pre1, own & (WAVE - 1), WAVE);
-            bool pass = false;
-            uint64_t key = 0;
-            if (p < totp) {
-                const int bpre = (own < WAVE) ? pa : pb;
-                const int slot = sh.bl_start[own] + (p - bpre);
-                float4 P = c.pts[slot];
-                // one 16-byte load: otherwise the compiler loads (z, w) first
-                // and (x, y) only for points that pass the depth test, two
-                // dependent loads in place of one
-                asm volatile("" : "+v"(P.x), "+v"(P.y), "+v"(P.z), "+v"(P.w));
-                if (P.z <= sh.bl_zmax[own] && P.z >= z_lo) {
-                    const float t = ray_param(P.x, P.y, P.z, g.dx, g.dy, g.dz);
-                    const float e2 = dist2_at(P.x, P.y, P.z, g.dx, g.dy, g.dz, t);
-                    const float rho = rho_at(c, g, t);
-                    pass = (P.z > 0.0f) & (t >= c.t_near) & (t <= c.t_far) & (e2 <= rho * rho);
-                    key = ((uint64_t)__float_as_uint(BY_E2 ? e2 : t) << 32) | __float_as_uint(P.w);
-                }
+            const int left = totp - p0;
+            const int slot_no = p0 + l + __shfl(shift, own, WAVE);
+            // (lanes past the end load the table's first point)
+            const float4 P = load_point(l < left ? slot_no : 0);
+            uint64_t in = left >= WAVE ? ~0ull : ~(~0ull << left);
+            if (deep) {
+                const float zm = __builtin_fminf(__shfl(zmax, own, WAVE), z_hi);
+                in &= ballot(P.z <= zm) & ballot(P.z >= z_lo);
             }
-            const bool live = pass && key >= lo;
-            count += popc64(ballot(live));
-            const bool keep = live && key < tau;
-            const uint64_t km = ballot(keep);
-            if (keep) sh.pend[npend + rank_below(km)] = key;
-            npend += popc64(km);
-            if (npend >= WAVE) flush(WAVE);
-            lds_sync();
+            test_points(in, P);
         }
+    };
+    // the points of one bucket per lane: slots at .. end - 1 (none: end <= at),
+    // depth bound zmax
+    auto sweep_buckets = [&](int at, int end, float zmax) {
+        uint64_t go = ballot(at < end);
+        while (popc64(go) >= 12) {
+            // (a lane without points left loads the table's first point)
+            const float4 P = load_point(at < end ? at : 0);
+            const uint64_t near = go & ballot(P.z <= __builtin_fminf(zmax, z_hi));
+            test_points(near & ballot(P.z >= z_lo), P);
+            // (points are ordered by depth: behind one too deep all are)
+            at = in_mask(near) ? at + 1 : end;
+            go = ballot(at < end);
+        }
+        if (go) sweep_flat(at, max(end - at, 0), true, zmax);
     };
 
-    // one window bucket at offset (dxi, dyi) from the pixel's bucket: returns
-    // whether it may hold a neighbour, and its slots
-    auto zmax_at = [&](float D) -> float {
-        // bounds only (margins of 1e-3 px and 0.1% dwarf 1-ulp approximations)
-        const float Dp = D - 0.01f;
-        if (Dp > 0.0f && Dp > dinf) {
-            const float zc = ((frL2 * __builtin_amdgcn_rcpf(Dp) + two_rw) * inv_L) * 1.001f + 1e-5f;
-            return zc < z_hi ? zc : z_hi;
-        }
-        return z_hi;
-    };
-    auto offset_D = [](int adx, int ady) -> float {
-        const float ex = __builtin_fmaxf(0.0f, (float)adx - 0.5f);
-        const float ey = __builtin_fmaxf(0.0f, (float)ady - 0.5f);
-        return __builtin_amdgcn_sqrtf(ex * ex + ey * ey);
-    };
-    auto probe = [&](bool valid, int dxi, int dyi, int &st, int &cnt, float &zmax) -> bool {
-        zmax = z_hi;
-        st = cnt = 0;
-        if (!valid) return false;
-        const int bx = gx + dxi, by = gy + dyi;
-        const float D = offset_D(dxi < 0 ? -dxi : dxi, dyi < 0 ? -dyi : dyi);
-        if (!(bx >= 0 && bx < Wg && by >= 0 && by < Hg && (square || D <= Dmax))) return false;
-        zmax = zmax_at(D);
-        const int key = bucket_of(Vg, c.layout, bx, by);
-        st = c.offsets[key];
-        cnt = c.offsets[key + 1] - st;
-        // the first depth is loaded with the offsets, not after them
-        const float z0 = c.bucket_z[key];
-        return cnt > 0 && z0 <= zmax;
-    };
-    auto append = [&](bool ok, int st, int cnt, float zmax) {
-        const uint64_t m = ballot(ok);
-        if (ok) {
-            const int pos = nbl + rank_below(m);
-            sh.bl_start[pos] = st;
-            sh.bl_cnt[pos] = cnt;
-            sh.bl_zmax[pos] = zmax;
-        }
-        nbl += popc64(m);
-        if (nbl >= WAVE) {
-            sweep_points(nbl);
-            nbl = 0;
-        }
-    };
-    // Larger windows: the buckets are culled by 8x8-bucket cells first: a cell whose
-    // nearest window bucket is at distance D is skipped when its minimum
-    // depth exceeds the depth bound at D (the bound only falls with D).
-    // Surviving cells are listed (up to 64 at a time, in the LDS the walk
-    // uses later) with the prefix of their window-bucket counts; each cell's
-    // buckets then go to one chunk of lanes, four cells per step.
-    // Small windows (most rays of object-scale scenes) skip the cell pass.
-    const int Wd = 2 * h + 1;
-    if (Wd * Wd <= 4 * WAVE) {
-        // (q + 0.5) / Wd is at least 0.5 / Wd from an integer, far more than
-        // the error of a float reciprocal, so the row index below is exact.
-        const float inv_wd = 1.0f / (float)Wd;
-        for (int q0 = 0; q0 < Wd * Wd; q0 += 2 * WAVE) {
-            const int qa = q0 + l, qb = q0 + WAVE + l;
-            const int ya = (int)(((float)qa + 0.5f) * inv_wd), yb = (int)(((float)qb + 0.5f) * inv_wd);
-            int stA, cntA, stB, cntB;
-            float zA, zB;
-            const bool okA = probe(qa < Wd * Wd, qa - ya * Wd - h, ya - h, stA, cntA, zA);
-            const bool okB = probe(qb < Wd * Wd, qb - yb * Wd - h, yb - h, stB, cntB, zB);
-            append(okA, stA, cntA, zA);
-            append(okB, stB, cntB, zB);
-        }
-        if (nbl > 0) sweep_points(nbl);
-        if (npend > 0) flush(npend);
-        return;
-    }
-    int4 *const cl = reinterpret_cast<int4 *>(sh.nb_p);  // (bx0, by0, width, prefix)
-    const int wx0 = max(gx - h, 0), wx1 = min(gx + h, Wg - 1);
+    const int wx0 = max(gx0 - h, 0), wx1 = min(gx1 + h, Wg - 1);
     const int wy0 = max(gy - h, 0), wy1 = min(gy + h, Hg - 1);
-    const int cx0 = wx0 >> CELL_SHIFT, cy0 = wy0 >> CELL_SHIFT;
-    const int ncw = (wx1 >> CELL_SHIFT) - cx0 + 1;
-    const int ncell = ncw * ((wy1 >> CELL_SHIFT) - cy0 + 1);
-    for (int c0 = 0; c0 < ncell; c0 += WAVE) {
-        const int ci = c0 + l;
-        bool keep = false;
-        int bx0 = 0, by0 = 0, bw = 0, nbk = 0;
-        if (ci < ncell) {
-            const int cyy = cy0 + ci / ncw, cxx = cx0 + ci % ncw;
-            bx0 = max(cxx << CELL_SHIFT, wx0);
-            by0 = max(cyy << CELL_SHIFT, wy0);
-            const int bx1 = min((cxx << CELL_SHIFT) + CELL - 1, wx1);
-            const int by1 = min((cyy << CELL_SHIFT) + CELL - 1, wy1);
-            bw = bx1 - bx0 + 1;
-            nbk = bw * (by1 - by0 + 1);
-            const int adx = gx < bx0 ? bx0 - gx : (gx > bx1 ? gx - bx1 : 0);
-            const int ady = gy < by0 ? by0 - gy : (gy > by1 ? gy - by1 : 0);
-            const float D = offset_D(adx, ady);
-            const float cz = __uint_as_float(c.cell_zmin[cell_base + cyy * ncx + cxx]);
-            keep = (square || D <= Dmax) && cz <= zmax_at(D);
+    bool runs = false;
+    if (h >= 0 && 2 * h + 1 <= ROW_WIN && c.layout != HP_LAYOUT_MORTON) {
+        const bool tiled = c.layout != HP_LAYOUT_ROWMAJOR;
+        const int ncol = tiled ? (wx1 >> 3) - (wx0 >> 3) + 1 : 1;  // at most 4
+        const int row = ncol == 1 ? l : ncol == 2 ? l >> 1 : ncol == 3 ? (l * 171) >> 9 : l >> 2;
+        const int col = l - row * ncol;
+        const int dyi = row - h, by = gy + dyi;
+        int st = 0, cnt = 0;
+        if (row <= 2 * h && by >= 0 && by < Hg) {
+            // half-width of the disc in this row (generous: bounds only)
+            int hw = h;
+            if (!square) {
+                const float ey = __builtin_fmaxf(0.0f, (float)(dyi < 0 ? -dyi : dyi) - 0.5f);
+                const float ex2 = Dmax * Dmax - ey * ey;
+                hw = ex2 >= 0.0f ? min(h, (int)(__builtin_amdgcn_sqrtf(ex2) * 1.0001f + 0.501f)) : -1 - ng;
+            }
+            int x0 = max(gx0 - hw, 0), x1 = min(gx1 + hw, Wg - 1);
+            if (tiled) {
+                const int tx = ((wx0 >> 3) + col) << 3;
+                x0 = max(x0, tx);
+                x1 = min(x1, tx + 7);
+            }
+            if (x0 <= x1) {
+                const int key = bucket_of(Vg, c.layout, x0, by);
+                st = c.offsets[key];
+                cnt = c.offsets[key + (x1 - x0) + 1] - st;
+            }
         }
-        const uint64_t km = ballot(keep);
-        if (km == 0) continue;
-        const int nk = keep ? nbk : 0;
-        const int inc = wave_incl_scan_i32(nk);
-        const int total = readlane_i32(inc, WAVE - 1);
-        lds_sync();
-        if (keep) cl[rank_below(km)] = make_int4(bx0, by0, bw, inc - nk);
-        lds_sync();
-        const int ncl = popc64(km);
-        // one listed cell per chunk of lanes (a cell holds at most 64
-        // buckets), four cells per step so that their loads overlap; the
-        // order in which buckets are appended does not change the kept keys
-        for (int k0 = 0; k0 < ncl; k0 += 4) {
-            bool v[4], ok[4];
-            int dx[4], dy[4], st[4], cnt[4];
-            float zm[4];
+        const int totp = readlane_i32(wave_incl_scan_i32(cnt), WAVE - 1);
+        runs = totp <= ROW_POINTS;
+        if (runs) sweep_flat(st, cnt, false, 0.0f);
+    }
+    if (h >= 0 && !runs) {
+        // depth bound of the window buckets at distance D from the rays' pixels
+        auto zmax_at = [&](float D) -> float {
+            // bounds only (margins of 1e-3 px and 0.1% dwarf 1-ulp approximations)
+            const float Dp = D - 0.01f;
+            const float zc = ((frL2 * __builtin_amdgcn_rcpf(Dp) + two_rw) * inv_L) * 1.001f + 1e-5f;
+            return (Dp > 0.0f) & (Dp > dinf) & (zc < z_hi) ? zc : z_hi;
+        };
+        // distance of buckets x .. x + nx, y .. y + ny from the nearest of the rays' pixel centres
+        auto distance = [&](int x, int y, int nx, int ny) -> float {
+            const int ax = max(max(x - gx1, gx0 - (x + nx)), 0), ay = max(max(y - gy, gy - (y + ny)), 0);
+            const float ex = __builtin_fmaxf(0.0f, (float)ax - 0.5f);
+            const float ey = __builtin_fmaxf(0.0f, (float)ay - 0.5f);
+            return __builtin_amdgcn_sqrtf(ex * ex + ey * ey);
+        };
+        // A cell whose nearest window bucket is at distance D is skipped when
+        // its minimum depth exceeds the depth bound at D (the bound only
+        // falls with D).  Surviving cells are listed (up to 64 at a time) with
+        // the prefix of their window-bucket counts; each cell's buckets go to
+        // one chunk of lanes, two cells per step so that their loads overlap.
+        const int cx0 = wx0 >> CELL_SHIFT, cy0 = wy0 >> CELL_SHIFT;
+        const int ncw = (wx1 >> CELL_SHIFT) - cx0 + 1;
+        const int ncell = ncw * ((wy1 >> CELL_SHIFT) - cy0 + 1);
+        int c0 = 0;                     // next cell to look at
+        int k0 = 0, ncl = 0, total = 0;  // next listed cell, their number, their buckets
+        int nbl = 0;                    // listed buckets
+        for (;;) {
+            while (nbl < WAVE) {
+                if (k0 >= ncl) {
+                    if (c0 >= ncell) break;
+                    const int ci = min(c0 + l, ncell - 1);
+                    const int cyy = cy0 + ci / ncw, cxx = cx0 + ci % ncw;
+                    const int bx0 = max(cxx << CELL_SHIFT, wx0), by0 = max(cyy << CELL_SHIFT, wy0);
+                    const int bx1 = min((cxx << CELL_SHIFT) + CELL - 1, wx1);
+                    const int by1 = min((cyy << CELL_SHIFT) + CELL - 1, wy1);
+                    const int bw = bx1 - bx0 + 1;
+                    const float D = distance(bx0, by0, bx1 - bx0, by1 - by0);
+                    const float cz = __uint_as_float(c.cell_zmin[cell_base + cyy * ncx + cxx]);
+                    uint64_t km = ballot(c0 + l < ncell) & ballot(cz <= zmax_at(D));
+                    if (!square) km &= ballot(D <= Dmax);
+                    const int nk = in_mask(km) ? bw * (by1 - by0 + 1) : 0;
+                    const int inc = wave_incl_scan_i32(nk);
+                    total = readlane_i32(inc, WAVE - 1);
+                    lds_sync();
+                    if (in_mask(km))
+                        sh.cl[rank_below(km)] = make_int2((bx0 - wx0) | ((by0 - wy0) << 16), bw | ((inc - nk) << 16));
+                    lds_sync();
+                    ncl = popc64(km);
+                    k0 = 0;
+                    c0 += WAVE;
+                    continue;
+                }
+                // (every lane loads, those outside the window the view's first
+                // bucket, so that the loads of both cells are in flight
+                // together: behind a branch each waits for the one before)
+                uint64_t in[2];
+                int key[2], at[2], end[2], off[2];
+                float zm[2], z0[2];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                v[u] = false;
-                dx[u] = dy[u] = 0;
-                if (k0 + u < ncl) {
-                    const int4 e = cl[k0 + u];
-                    const int nin = (k0 + u + 1 < ncl ? cl[k0 + u + 1].w : total) - e.w;
-                    if (l < nin) {
-                        const int ry = (int)(((float)l + 0.5f) * __builtin_amdgcn_rcpf((float)e.z));
-                        dx[u] = e.x + (l - ry * e.z) - gx;
-                        dy[u] = e.y + ry - gy;
-                        v[u] = true;
-                    }
+                for (int u = 0; u < 2; ++u) {
+                    const int2 e = sh.cl[min(k0 + u, ncl - 1)];
+                    const int next = sh.cl[min(k0 + u + 1, ncl - 1)].y >> 16;
+                    const int nin = (k0 + u + 1 < ncl ? next : total) - (e.y >> 16);
+                    const int bw = e.y & 0xffff;
+                    const int ry = (int)(((float)l + 0.5f) * __builtin_amdgcn_rcpf((float)bw));
+                    const int ox = (e.x & 0xffff) + (l - ry * bw), oy = (int)((uint32_t)e.x >> 16) + ry;
+                    const float D = distance(wx0 + ox, wy0 + oy, 0, 0);
+                    in[u] = k0 + u < ncl ? ballot(l < nin) : 0ull;
+                    if (!square) in[u] &= ballot(D <= Dmax);
+                    zm[u] = zmax_at(D);
+                    off[u] = ox | (oy << 16);
+                    key[u] = in_mask(in[u]) ? bucket_of(Vg, c.layout, wx0 + ox, wy0 + oy) : Vg.bucket_base;
+                    at[u] = c.offsets[key[u]];
+                    end[u] = c.offsets[key[u] + 1];
+                    z0[u] = c.bucket_z[key[u]];
+                }
+                k0 += 2;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const uint64_t m = in[u] & ballot(end[u] > at[u]) & ballot(z0[u] <= zm[u]);
+                    if (in_mask(m)) sh.bl[nbl + rank_below(m)] = make_int2(key[u], off[u]);
+                    nbl += popc64(m);
                 }
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) ok[u] = probe(v[u], dx[u], dy[u], st[u], cnt[u], zm[u]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) append(ok[u], st[u], cnt[u], zm[u]);
+            if (nbl == 0) break;
+            // the last (up to) 64 of the list
+            const int take = min(nbl, WAVE);
+            nbl -= take;
+            lds_sync();
+            int at = 0, end = 0;
+            float zmax = 0.0f;
+            if (l < take) {
+                const int2 e = sh.bl[nbl + l];
+                at = c.offsets[e.x];
+                end = c.offsets[e.x + 1];
+                zmax = zmax_at(distance(wx0 + (e.y & 0xffff), wy0 + (int)((uint32_t)e.y >> 16), 0, 0));
+            }
+            lds_sync();
+            sweep_buckets(at, end, zmax);
         }
     }
-    if (nbl > 0) sweep_points(nbl);
-    if (npend > 0) flush(npend);
+#pragma unroll
+    for (int r = 0; r < G; ++r) {
+        if (r >= ng) break;
+        if (np[r] > most) (void)keep_smallest<HELD + WAVE>(sh.pend[s0 + r], np[r], want, most - want);
+        if (l == 0) {
+            slot[s0 + r].n = np[r];
+            slot[s0 + r].count = count[r];
+        }
+    }
+    lds_sync();
 }
 
 // Merge two ascending KT-lists and keep the KT smallest, ascending: the
@@ -829,7 +1123,7 @@ __device__ __forceinline__ void sort8(uint64_t (&x)[8])
 // lo + q + 4, ... into an ascending register list of (dist^2 bits << 32 |
 // index); the quad then merges its four lists (DPP within the quad).
 template <int KT>
-__device__ __forceinline__ void knn_window(const RayGeom &g, const SearchLds &sh, float tq, float R2,
+__device__ __forceinline__ void knn_window(const RayGeom &g, const SlabList &sh, float tq, float R2,
                                            int lo, int hi, uint64_t (&kd)[KT])
 {
     const int q = lane_id() & 3;
@@ -1018,44 +1312,6 @@ __device__ __forceinline__ void knn_window(const RayGeom &g, const SearchLds &sh
     merge_low<KT>(kd, other);
 }
 
-// Nearest neighbours of 16 candidates at once.  Lane l = 4 g + q serves
-// candidate c0 + g; its four lanes split the candidate's t-window of the
-// sorted list (entries within R_j in t), each keeping an ascending register
-// list, merged across the quad.  On return every lane of the quad holds the
-// candidate's KT smallest keys (KEY_NONE = none).
-template <int KT>
-__device__ __forceinline__ void knn_quad(const SearchCtx &c, const RayGeom &g, const SearchLds &sh,
-                                         int j, int m, uint64_t (&kd)[KT])
-{
-    const bool active = j < m;
-    float tj = 0.0f, R2 = 0.0f;
-    int lo = 0, hi = 0;
-    if (active) {
-        tj = sh.nb_t[j];
-        const float Rj = rho_at(c, g, tj);
-        R2 = Rj * Rj;
-        // |t_i - t_j| > span implies dist^2 > R_j^2 (margins above rounding)
-        const float span = Rj * 1.001f + tj * 4e-6f + 1e-7f;
-        const float tlo = tj - span, thi = tj + span;
-        int a = 0, b = j;  // first index with t >= tlo
-        while (a < b) {
-            const int mid = (a + b) >> 1;
-            if (sh.nb_t[mid] < tlo) a = mid + 1;
-            else b = mid;
-        }
-        lo = a;
-        a = j + 1;
-        b = m;  // first index with t > thi
-        while (a < b) {
-            const int mid = (a + b) >> 1;
-            if (sh.nb_t[mid] <= thi) a = mid + 1;
-            else b = mid;
-        }
-        hi = a;
-    }
-    knn_window<KT>(g, sh, tj, R2, lo, hi, kd);
-}
-
 // Distances of a quad's list entries split over its lanes: lane q takes the
 // correctly rounded square roots of entries k = q, q + 4, ... (dq[e] for
 // k = 4 e + q), so no lane computes more than KT / 4 of them.  Lane-local
@@ -1080,103 +1336,338 @@ __device__ __forceinline__ void quad_list_sqrt(const uint64_t (&kd)[KT], float (
         dq[e] = __builtin_sqrtf(__uint_as_float((uint32_t)(quad_entry<KT>(kd, e) >> 32)));
 }
 
-// Candidate walk.  Candidates (the neighbours in (t, index) order) are
-// processed 16 at a time, candidate c0 + g on lanes 4 g .. 4 g + 3.  After a
-// chunk's transmittance walk, emit(s, q, tj, kd, kc) is called on the four
-// lanes (q = 0..3) of every candidate that became sample s, with its K nearest
-// neighbours kd (ascending (dist^2 bits, index), KEY_NONE = none), their number kc
-// and the lane's share dq of their distances (quad_list_sqrt).  Returns the sample count and sets first_idx to the primary point.
-template <int KT, typename Emit>
-__device__ __forceinline__ int walk_candidates(const SearchCtx &c, const RayGeom &g, SearchLds &sh,
-                                               uint64_t top, int m, int &first_idx, Emit emit)
+// Sort of 16 R keys per row of 16 lanes, R per lane (key e of lane k is element
+// R k + e when it returns): bitonic merges in the form that compares with the
+// mirrored element first, so that every exchange leaves the smaller key at
+// the lower element and no block descends.  Four rays' 64 keys each sort at
+// once for little more than a wave takes to sort 64 keys one per lane.
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v)
 {
-    const int l = lane_id();
+    const uint32_t a = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)v, CTRL, 0xF, 0xF, false);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), CTRL, 0xF, 0xF, false);
+    return ((uint64_t)b << 32) | a;
+}
+
+// lane patterns of the exchanges: the lane's neighbour at distance 1, 2, and
+// the mirror of its block of 4, 8 and 16 lanes, and the neighbour at distance 8
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_REV4 = 0x1B, DPP_REV8 = 0x141, DPP_REV16 = 0x140, DPP_ROR8 = 0x128;
+
+// One exchange between lanes: the smaller key of each pair on the lanes whose
+// index bit BIT is clear, the larger on the others.  MIRROR pairs element e
+// with the partner lane's element R - 1 - e.
+template <int R, int BIT, int CTRL, bool MIRROR, int CTRL2 = 0>
+__device__ __forceinline__ void row_exchange(uint64_t (&x)[R])
+{
+    uint64_t o[R];
+#pragma unroll
+    for (int e = 0; e < R; ++e) {
+        o[e] = dpp_u64<CTRL>(x[MIRROR ? R - 1 - e : e]);
+        if constexpr (CTRL2 != 0) o[e] = dpp_u64<CTRL2>(o[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < R; ++e) {
+        const bool take = (key_f64(o[e]) < key_f64(x[e])) != lanes_in<lane_bit_mask(BIT)>();
+        x[e] = take ? o[e] : x[e];
+    }
+}
+
+// half-cleaners inside every lane
+template <int R>
+__device__ __forceinline__ void lane_merge(uint64_t (&x)[R])
+{
+#pragma unroll
+    for (int h = R / 2; h > 0; h >>= 1)
+#pragma unroll
+        for (int e = 0; e < R; ++e)
+            if ((e & h) == 0) kswap(x[e], x[e + h]);
+}
+
+template <int R>
+__device__ __forceinline__ void row_sort(uint64_t (&x)[R])
+{
+    static_assert(R == 4 || R == 8, "four or eight keys per lane");
+    if constexpr (R == 8) {
+        sort8(x);
+    } else {
+        kswap(x[0], x[1]);
+        kswap(x[2], x[3]);
+        kswap(x[0], x[2]);
+        kswap(x[1], x[3]);
+        kswap(x[1], x[2]);
+    }
+    // blocks of 2, 4, 8, 16 lanes
+    row_exchange<R, 0, DPP_XOR1, true>(x);
+    lane_merge(x);
+    row_exchange<R, 1, DPP_REV4, true>(x);
+    row_exchange<R, 0, DPP_XOR1, false>(x);
+    lane_merge(x);
+    row_exchange<R, 2, DPP_REV8, true>(x);
+    row_exchange<R, 1, DPP_XOR2, false>(x);
+    row_exchange<R, 0, DPP_XOR1, false>(x);
+    lane_merge(x);
+    row_exchange<R, 3, DPP_REV16, true>(x);
+    // (lanes 4 apart: the mirror of 8 lanes, its halves mirrored back)
+    row_exchange<R, 2, DPP_REV8, false, DPP_REV4>(x);
+    row_exchange<R, 1, DPP_XOR2, false>(x);
+    row_exchange<R, 0, DPP_XOR1, false>(x);
+    lane_merge(x);
+}
+
+// Exchanges between lanes of different rows.
+template <int R, int BIT, bool MIRROR>
+__device__ __forceinline__ void wave_exchange(uint64_t (&x)[R], int xor_lane)
+{
+    uint64_t o[R];
+#pragma unroll
+    for (int e = 0; e < R; ++e) {
+        const uint64_t v = x[MIRROR ? R - 1 - e : e];
+        const uint32_t a = (uint32_t)__shfl_xor((int)(uint32_t)v, xor_lane, WAVE);
+        const uint32_t b = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), xor_lane, WAVE);
+        o[e] = ((uint64_t)b << 32) | a;
+    }
+#pragma unroll
+    for (int e = 0; e < R; ++e) {
+        const bool take = (key_f64(o[e]) < key_f64(x[e])) != lanes_in<lane_bit_mask(BIT)>();
+        x[e] = take ? o[e] : x[e];
+    }
+}
+
+// Sort of 64 R keys across the wave (key e of lane l is element R l + e when
+// it returns): the rows, then blocks of two and of four rows.
+template <int R>
+__device__ __forceinline__ void wave_sort_many(uint64_t (&x)[R])
+{
+    row_sort(x);
+    wave_exchange<R, 4, true>(x, 31);
+    row_exchange<R, 3, DPP_ROR8, false>(x);
+    row_exchange<R, 2, DPP_REV8, false, DPP_REV4>(x);
+    row_exchange<R, 1, DPP_XOR2, false>(x);
+    row_exchange<R, 0, DPP_XOR1, false>(x);
+    lane_merge(x);
+    wave_exchange<R, 5, true>(x, 63);
+    wave_exchange<R, 4, false>(x, 16);
+    row_exchange<R, 3, DPP_ROR8, false>(x);
+    row_exchange<R, 2, DPP_REV8, false, DPP_REV4>(x);
+    row_exchange<R, 1, DPP_XOR2, false>(x);
+    row_exchange<R, 0, DPP_XOR1, false>(x);
+    lane_merge(x);
+}
+
+// Keys 4 k .. 4 k + 3 of the ascending list of the row's ray (KEY_NONE = none)
+// on lane k of each row of 16 lanes, from the row of `pend` that holds `held`
+// <= 128 keys in no order (which may be overwritten); `most`: the largest
+// number held by a row.
+__device__ __forceinline__ void row_sorted_keys(uint64_t *pend, int held, int most, uint64_t (&key)[4])
+{
+    const int k16 = phase_lane_id() & 15;
+    if (most <= WAVE) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) key[e] = 16 * e + k16 < held ? pend[16 * e + k16] : KEY_NONE;
+        row_sort(key);
+        return;
+    }
+    uint64_t x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = 16 * e + k16 < held ? pend[16 * e + k16] : KEY_NONE;
+    row_sort(x);
     lds_sync();
-    if (l < m) {
-        const int idxj = (int)(uint32_t)top;
-        sh.nb_p[l] = c.pcam[(int64_t)g.vi * c.n_points + idxj];
-        sh.nb_t[l] = __uint_as_float((uint32_t)(top >> 32));
+    if (k16 < 8) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pend[8 * k16 + e] = x[e];
     }
     lds_sync();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) key[e] = pend[4 * k16 + e];
+}
+
+// Candidate walk of up to four rays at once, one row of 16 lanes each: lane
+// 16 r + k serves candidate c0 + k of ray r (the neighbours in (t, index)
+// order, 16 at a time).  One lane per candidate rather than four: the search
+// kernels are bound by vector instructions, and the sorting networks, square
+// roots and the transmittance products below cost a wave the same whether its
+// lanes serve one ray or four.
+//
+// Nearest neighbours.  A lane takes the list in batches of eight consecutive
+// entries, first those around its candidate, then on the side whose next
+// entry is nearer in t, until both next entries lie further than R_j or than
+// its KT-th distance so far (distance >= |t_i - t_j| up to rounding); each
+// batch is sorted (19 compare-exchanges) and merged into the lane's ascending
+// list of (dist^2 bits << 32 | index).
+//
+// Transmittance (Eq. 5).  The value in front of each candidate is the running
+// product of (1 - alpha) in candidate order, one binary32 multiply after
+// another as a sequential walk takes them: fifteen steps in which every lane
+// takes its left neighbour's value times that neighbour's factor, the row's
+// first lane keeping the value carried from the previous sixteen.  A lane's
+// value is final once its left neighbour's is.
+//
+// The rays are those of the first ns slots, their keys in sh.pend; lists(ray,
+// i, m, count, key) is called on every lane of theirs with entries i .. i + 3
+// of the ray's list of m neighbours.
+//
+// emit(ray, s, tj, kd, dist, kc) is called on the lane of every candidate that
+// became sample s, with its nearest neighbours kd (ascending, an empty slot's
+// upper half is KEY_NONE's), their distances and their number kc among the
+// first K; first(ray, index) on the lane of a ray's first sample, and
+// ends(ray, n) on a ray's first lane with its sample count.
+template <int KT, typename Lists, typename Emit, typename First, typename Ends>
+__device__ __forceinline__ void walk_batch(WalkLds &sh, int ns, Lists lists, Emit emit, First first, Ends ends)
+{
+    const SearchCtx c = phase_ctx();
+    const int l = phase_lane_id(), r = l >> 4, k16 = l & 15;
+    const bool live = r < ns;
+    const RaySlot me = sh.slot[live ? r : 0];
+    const int held = live ? me.n : 0, m = min(held, c.M), ray = me.ray;
+    RayGeom g;
+    {
+        const RayGeom &gr = sh.rs[me.rs];
+        g.dx = gr.dx;
+        g.dy = gr.dy;
+        g.dz = gr.dz;
+        g.kappa = gr.kappa;
+        g.vi = gr.vi;
+    }
+    float4 *const nb = sh.lists().p;
+    const float nan = __builtin_nanf("");
+    {
+        uint64_t key[4];
+        int most = held;
+        most = max(most, __shfl_xor(most, 16, WAVE));
+        most = uniform_i32(max(most, __shfl_xor(most, 32, WAVE)));
+        row_sorted_keys(sh.search().pend[r], held, most, key);
+        if (live) lists(ray, 4 * k16, m, me.count, key);
+        float4 P[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            P[e] = make_float4(nan, nan, nan, 0.0f);
+            if (4 * k16 + e < m) P[e] = c.pcam[(int64_t)g.vi * c.n_points + (int)(uint32_t)key[e]];
+        }
+        lds_sync();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) nb[WALK_PAD + WALK_STRIDE * r + 4 * k16 + e] = P[e];
+        if (l < WALK_PAD * (GROUP + 1))
+            nb[WALK_STRIDE * (l / WALK_PAD) + l % WALK_PAD] = make_float4(nan, nan, nan, 0.0f);
+    }
+    lds_sync();
+    const float4 *const row = nb + WALK_PAD + WALK_STRIDE * r;
+    auto t_at = [&](int i) {
+        const float4 P = row[i];
+        return ray_param(P.x, P.y, P.z, g.dx, g.dy, g.dz);
+    };
     float T = 1.0f;
     int sel = 0;
-    first_idx = -1;
-    bool done = false;
-    for (int c0 = 0; c0 < m && !done; c0 += 16) {
-        const int j = c0 + (l >> 2);
+    bool done = m == 0;
+    for (int c0 = 0;; c0 += 16) {
+        const int j = c0 + k16;
+        const bool active = !done && j < m;
+        if (!ballot(active)) break;
         uint64_t kd[KT];
-        knn_quad<KT>(c, g, sh, j, m, kd);
-        // each lane takes a quarter of the square roots; the quad then shares
-        // them so that every lane sums all of them in list order
-        float dq[KT / 4], dist[KT];
-        quad_list_sqrt<KT>(kd, dq);
 #pragma unroll
-        for (int k = 0; k < KT; ++k)
-            dist[k] = __uint_as_float(quad_bcast_u32(__float_as_uint(dq[k >> 2]), k & 3));
-        // the list's valid entries (key != ~0) form a prefix; the first K count
+        for (int k = 0; k < KT; ++k) kd[k] = KEY_NONE;
+        float alpha = 0.0f, tj = 0.0f, dist[KT];
         int kc = 0;
-#pragma unroll
-        for (int k = 0; k < KT; ++k) kc += kd[k] != KEY_NONE ? 1 : 0;
-        kc = min(kc, c.K);
-        float alpha = 0.0f, tj = 0.0f;
-        if (j < m) {
-            tj = sh.nb_t[j];
+        if (active) {
+            tj = t_at(j);
             const float Rj = rho_at(c, g, tj);
+            const float R2 = Rj * Rj;
+            const float slack = (tj + Rj) * 4e-6f + 1e-7f;
+            auto take8 = [&](int base, uint64_t(&x)[8]) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (e == 4) asm volatile("" ::: "memory");
+                    const float4 P = row[base + e];
+                    const float d2 = dist2_at(P.x, P.y, P.z, g.dx, g.dy, g.dz, tj);
+                    const uint32_t hi = d2 <= R2 ? __float_as_uint(d2) : (uint32_t)(KEY_NONE >> 32);
+                    x[e] = ((uint64_t)hi << 32) | __float_as_uint(P.w);
+                }
+                sort8(x);
+            };
+            int lo = max(j - 4, 0), hi = lo + 8;
+            {
+                uint64_t x[8];
+                take8(lo, x);
+#pragma unroll
+                for (int k = 0; k < KT && k < 8; ++k) kd[k] = x[k];
+            }
+            for (;;) {
+                // (a missing entry's t is NaN: neither comparison holds; an
+                // unfilled list's last distance is NaN and the minimum R_j)
+                const float dk = __uint_as_float((uint32_t)(kd[KT - 1] >> 32));
+                const float reach = __builtin_fminf(Rj, __builtin_amdgcn_sqrtf(dk)) * 1.001f + slack;
+                const float du = t_at(hi) - tj, dd = tj - t_at(lo - 1);
+                const bool up = du <= reach, dn = dd <= reach;
+                if (!(up | dn)) break;
+                const bool go_up = up && (!dn || du <= dd);
+                const int base = go_up ? hi : lo - 8;
+                uint64_t x[8];
+                take8(base, x);
+                hi = go_up ? hi + 8 : hi;
+                lo = go_up ? lo : lo - 8;
+                if constexpr (KT <= 8) {
+#pragma unroll
+                    for (int k = 0; k < KT; ++k) kd[k] = kmin(kd[k], x[KT - 1 - k]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) kd[KT - 8 + e] = kmin(kd[KT - 8 + e], x[7 - e]);
+                }
+                // kd is bitonic and holds the KT smallest: half-cleaners sort it
+#pragma unroll
+                for (int h = KT / 2; h > 0; h >>= 1) {
+#pragma unroll
+                    for (int k = 0; k < KT; ++k)
+                        if ((k & h) == 0) kswap(kd[k], kd[k + h]);
+                }
+            }
+            // the list's valid entries form a prefix; the first K count
             float sum = 0.0f;  // (adding +0 past the prefix leaves it unchanged)
 #pragma unroll
-            for (int k = 0; k < KT; ++k) sum = sum + (k < kc ? dist[k] : 0.0f);
+            for (int k = 0; k < KT; ++k) {
+                const uint32_t hi32 = (uint32_t)(kd[k] >> 32);
+                const bool v = hi32 != (uint32_t)(KEY_NONE >> 32) && k < c.K;
+                dist[k] = v ? __builtin_sqrtf(__uint_as_float(hi32)) : 0.0f;
+                kc += v ? 1 : 0;
+                sum = sum + dist[k];
+            }
             const float dj = (sum + (float)(c.K - kc) * Rj) / (float)c.K;
             const float uj = (dj * dj) * c.inv_beta2;
             alpha = c.gamma * exp_neg(-uj);
         }
-        // transmittance walk over this chunk (Eq. 5).  The transmittance in
-        // front of each candidate is the running product of (1 - alpha) in
-        // candidate order, one binary32 multiply after another as a sequential
-        // walk takes them (candidates past the list have alpha = 0, a factor
-        // of exactly 1); the value in front of each candidate reaches its quad
-        // through the LDS.
-        const int gl = l >> 2;
-        const int ncand = min(c0 + 16, m) - c0;
-        const int sel0 = sel;
-        float *const tb = reinterpret_cast<float *>(sh.pend);  // (free during the walk)
+        // (candidates past the list have alpha = 0, a factor of exactly 1)
+        const float f = 1.0f - alpha;
+        const float fs = __int_as_float(__builtin_amdgcn_update_dpp(
+            0x3f800000, __float_as_int(f), 0x111, 0xF, 0xF, false));  // left neighbour's, 1 on first lanes
+        float Tb = T;
 #pragma unroll
-        for (int gg = 0; gg < 16; ++gg) {
-            const float aj = readlane_f32(alpha, 4 * gg);
-            if (l == 0) tb[gg] = T;
-            T = T * (1.0f - aj);
+        for (int k = 0; k < 15; ++k) {
+            const int left = __builtin_amdgcn_update_dpp(__float_as_int(Tb), __float_as_int(Tb), 0x111, 0xF, 0xF, false);
+            Tb = __int_as_float(left) * fs;
         }
-        lds_sync();
-        const float Tb = tb[gl];
-        // the sequential walk's decisions, one candidate per quad leader:
-        // selected when its weight passes eps_w while fewer than S samples
-        // are taken; it stops after the S-th sample or once gamma T <= eps_w
-        const float wq = alpha * Tb;
-        const float Ta = Tb * (1.0f - alpha);
-        const bool lead = (l & 3) == 0 && gl < ncand;
-        const uint64_t pm = ballot(lead && wq > c.eps_w);         // bit 4 g
-        const uint64_t dm = ballot(lead && c.gamma * Ta <= c.eps_w);
-        int stop = dm ? __builtin_ctzll(dm) : WAVE;
-        const int room = c.S - sel0;
-        if (popc64(pm) >= room) {
-            uint64_t x = pm;
-            for (int k = 1; k < room; ++k) x &= x - 1ull;
-            stop = min(stop, __builtin_ctzll(x));
+        const float Ta = Tb * f;
+        // the sequential walk's decisions: a candidate is visited if no
+        // earlier one left gamma T <= eps_w behind it and fewer than S
+        // samples were taken before it, and selected if its weight passes
+        const uint64_t am = ballot(active);
+        const uint64_t pm = am & ballot(alpha * Tb > c.eps_w);
+        const uint64_t dm = am & ballot(c.gamma * Ta <= c.eps_w);
+        const uint32_t prow = (uint32_t)(pm >> (16 * r)) & 0xffffu;
+        const uint32_t drow = (uint32_t)(dm >> (16 * r)) & 0xffffu;
+        const uint32_t below = (1u << k16) - 1u;
+        const int rank = sel + __popc(prow & below);
+        const bool mine = ((prow >> k16) & 1u) != 0 && (drow & below) == 0 && rank < c.S;
+        if (mine) {
+            if (rank == 0) first(ray, __float_as_int(row[j].w));
+            emit(ray, rank, tj, kd, dist, kc);
         }
-        if (stop < WAVE) done = true;
-        const uint64_t smask = stop < WAVE ? pm & ((2ull << stop) - 1ull) : pm;
-        sel += popc64(smask);
-        if (smask) {
-            if (sel0 == 0) {
-                const int gsel = __builtin_ctzll(smask) >> 2;
-                first_idx = __float_as_int(sh.nb_p[c0 + gsel].w);
-            }
-            // (the rank from the lane's own position: a per-lane mask would be
-            // kept, and spilled, for the whole kernel)
-            if ((smask >> (l & ~3)) & 1ull)
-                emit(sel0 + rank_below(smask) - ((l & 3) ? 1 : 0), l & 3, tj, kd, dq, kc);
-        }
+        // the row's totals on all of its lanes
+        const uint64_t sm = ballot(mine);
+        sel += __popc((uint32_t)(sm >> (16 * r)) & 0xffffu);
+        done = done || drow != 0 || sel >= c.S || c0 + 16 >= m;
+        // the last lane's value behind it is carried to the whole row
+        T = __int_as_float(__shfl(__float_as_int(Ta), l | 15, WAVE));
     }
-    return sel;
+    if (live && k16 == 0) ends(ray, sel);
+    lds_sync();
 }
 
 __device__ __forceinline__ int wave_min_i32(int v)
@@ -1190,27 +1681,92 @@ __device__ __forceinline__ int wave_min_i32(int v)
     return v;
 }
 
+// A ray's neighbours in depth order, 64 at a time.  Where the search held all
+// of them (up to HELD_SLAB), they are sorted once and a slab is a range of
+// that list; else the ray is searched again for each slab, with the slab's
+// bound as a filter.
+struct SlabKeys {
+    uint64_t keys;  // the current slab, one key per lane, ascending (n of them)
+    int n;
+    int rest;       // neighbours at or above the slab's first key (any number above n where there are more)
+    int held;       // keys in the sorted list, -1: not all neighbours are held
+};
+
+__device__ __forceinline__ void slab_from(SlabLds &lds, SlabKeys &k, uint64_t from)
+{
+    const int l = phase_lane_id();
+    lds_sync();
+    if (k.held >= 0) {
+        int at = 0;
+#pragma unroll
+        for (int e = 0; e < HELD_SLAB / WAVE; ++e)
+            at += popc64(ballot(WAVE * e + l < k.held) & ballot(lds.s.pend[0][WAVE * e + l] < from));
+        k.rest = k.held - at;
+        k.n = min(k.rest, WAVE);
+        k.keys = l < k.n ? lds.s.pend[0][at + l] : ~0ull;
+        return;
+    }
+    search_group<1, HELD_SLAB>(lds.rs, lds.slot, lds.s, 0, 1, WAVE, WAVE, from);
+    k.rest = uniform_i32(lds.slot[0].count);
+    k.n = min(k.rest, WAVE);
+    k.keys = wave_sort_fast(l < k.n ? lds.s.pend[0][l] : ~0ull);
+}
+
+// The first slab of the ray in slot 0 (its record: rec).
+__device__ __forceinline__ void first_slab(SlabLds &lds, SlabKeys &k, int rec)
+{
+    const int l = phase_lane_id();
+    lds_sync();
+    if (l == 0) lds.slot[0].rs = rec;
+    lds_sync();
+    search_group<1, HELD_SLAB>(lds.rs, lds.slot, lds.s, 0, 1, WAVE, HELD_SLAB);
+    k.rest = uniform_i32(lds.slot[0].count);
+    const int held = uniform_i32(lds.slot[0].n);
+    k.held = held == k.rest ? held : -1;
+    k.n = min(k.rest, WAVE);
+    if (held <= WAVE) {
+        k.keys = wave_sort_fast(l < held ? lds.s.pend[0][l] : ~0ull);
+        lds.s.pend[0][l] = k.keys;
+        lds_sync();
+        return;
+    }
+    constexpr int R = HELD_SLAB / WAVE;
+    uint64_t x[R];
+#pragma unroll
+    for (int e = 0; e < R; ++e) x[e] = WAVE * e + l < held ? lds.s.pend[0][WAVE * e + l] : KEY_NONE;
+    wave_sort_many(x);
+    lds_sync();
+#pragma unroll
+    for (int e = 0; e < R; ++e) lds.s.pend[0][R * l + e] = x[e];
+    lds_sync();
+    k.keys = lds.s.pend[0][l];
+}
+
 // Uniform multi-surface sampling (the baseline of Sec. 3.5): positions
 // t_k = t_near + (k + 1/2) step, k < ms_steps, each with a radius search: a
 // position is a sample when some neighbour of the ray (any of them, not only
 // the first m_cap) lies within R_k = rho(t_k) of it (the exact test), in
 // depth order up to S, with its K nearest such neighbours.  The neighbours
-// are walked in depth order 64 at a time: a slab is the 64 smallest keys at
-// or above a bound (search_neighbours with `lo`), kept sorted in the LDS.
+// are walked in depth order 64 at a time (SlabKeys, the first slab as
+// first_slab left it), their points in the LDS.
 // Positions go 16 at a time, one per quad (lanes 4 g .. 4 g + 3), each
 // keeping its K nearest over the slabs that reach its window |t - t_k| <= R_k
 // (distance >= |t_i - t_k| up to rounding); a batch starts from the slab of
 // keys at or above its first window and jumps over positions that no
-// neighbour can reach.  emit() as for the candidate walk; first_idx is the
-// nearest point of the first sample.  top, count: the ray's first slab and
-// neighbour count, as search_neighbours returned them.
+// neighbour can reach.  emit(s, q, tj, kd, dq, kc) is called on the four lanes
+// (q = 0..3) of every position that became sample s, with its nearest
+// neighbours kd (ascending, KEY_NONE = none), the lane's share dq of their
+// distances (quad_list_sqrt) and their number kc; first_idx is the nearest
+// point of the first sample.
 template <int KT, typename Emit>
-__device__ __forceinline__ int uniform_samples(const SearchCtx &c, const RayGeom &g, SearchLds &sh,
-                                               uint64_t top, int count, int &first_idx, Emit emit)
+__device__ __forceinline__ int uniform_samples(const RayGeom &g, SlabLds &lds, SlabKeys &slab, int &first_idx,
+                                               Emit emit)
 {
+    const SearchCtx c = phase_ctx();
     const int l = lane_id();
+    SlabList &sh = lds.list;
     first_idx = -1;
-    if (count == 0) return 0;
+    if (slab.rest == 0) return 0;
     const int nk = c.ms_steps;
     const float step = (c.t_far - c.t_near) / (float)nk;
     auto pos_t = [&](int k) { return fma_rn((float)k + 0.5f, step, c.t_near); };
@@ -1224,8 +1780,8 @@ __device__ __forceinline__ int uniform_samples(const SearchCtx &c, const RayGeom
         f = __builtin_fminf(__builtin_fmaxf(f, -2.0f), (float)nk + 2.0f);
         return max((int)__builtin_floorf(f) - 1, 0);
     };
-    uint64_t keys = top;  // the current slab, one key per lane
-    int n = count < WAVE ? count : WAVE, rest = count;
+    uint64_t &keys = slab.keys;
+    int &n = slab.n, &rest = slab.rest;
     auto load_slab = [&]() {
         lds_sync();
         if (l < n) {
@@ -1283,8 +1839,7 @@ __device__ __forceinline__ int uniform_samples(const SearchCtx &c, const RayGeom
             // ends beyond the last window of the batch
             if (rest <= n || sh.nb_t[n - 1] > t_end) break;
             const uint64_t last = readlane_u64(keys, n - 1);
-            search_neighbours(c, g, sh, keys, rest, last + 1ull);
-            n = rest < WAVE ? rest : WAVE;
+            slab_from(lds, slab, last + 1ull);
             load_slab();
         }
         const bool kept = active && kd[0] != KEY_NONE;
@@ -1312,9 +1867,8 @@ __device__ __forceinline__ int uniform_samples(const SearchCtx &c, const RayGeom
         if (!(sh.nb_t[0] <= tlo && rest <= n)) {
             // (the current slab does not hold every key from tlo on)
             const uint64_t lo_key = tlo > 0.0f ? ((uint64_t)__float_as_uint(tlo) << 32) : 0ull;
-            search_neighbours(c, g, sh, keys, rest, lo_key);
+            slab_from(lds, slab, lo_key);
             if (rest == 0) break;
-            n = rest < WAVE ? rest : WAVE;
             load_slab();
         }
         const int j = slab_lower(tlo);

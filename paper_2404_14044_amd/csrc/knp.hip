@@ -3,58 +3,71 @@
 // search with the kept list ordered by (squared distance to the ray, index),
 // blended with geometric weights w_i = 1 / max(e_i, eps), normalised.
 //
-// One 64-lane workgroup per ray, persistent over XCD-banded chunks like the
-// forward search: lane i < K holds the i-th nearest point, gathers its
-// colour, and the wave reduces the weighted sums with a fixed butterfly.
+// One wave searches up to four neighbouring rays at a time, as the forward
+// search does, and blends them one row of 16 lanes each: lane k of a row holds
+// the points 4 k .. 4 k + 3 nearest to its ray and gathers their colours, and
+// the row adds up the weighted sums pairwise in list order.
 #include "hp_kernels.hpp"
 #include "hp_search.hpp"
 
 namespace hp {
 
-__device__ __forceinline__ float wave_sum_f32(float v)
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_knp(SearchCtx, KnpArgs)
 {
+    __shared__ KnpLds sh;
+    for_each_group_banded<GROUP>(sh.rs, [&](int n, int ray0, int rec, bool) {
+        lds_sync();
+        if (lane_id() < n) sh.slot[lane_id()].rs = rec + lane_id();
+        lds_sync();
+        search_group<GROUP, HELD_KNP, true>(sh.rs, sh.slot, sh.s, 0, n, phase_arg<KnpArgs>().K, WAVE);
+        const KnpArgs a = phase_arg<KnpArgs>();
+        const int l = phase_lane_id(), r = l >> 4, k16 = l & 15;
+        const bool live = r < n;
+        const RaySlot me = sh.slot[live ? r : 0];
+        const int held = live ? me.n : 0, kk = live ? min(me.count, a.K) : 0;
+        const int64_t ray = ray0 + r;
+        uint64_t key[4];
+        row_sorted_keys(sh.s.pend[r], held, WAVE, key);
+        float d[4], w[4], c0[4], c1[4], c2[4];
 #pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) v += __shfl_xor(v, o, WAVE);
-    return v;
-}
-
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)))
-k_knp(SearchCtx c, KnpArgs a)
-{
-    __shared__ SearchLds sh;
-    const int l = lane_id();
-    for_each_ray_banded(c, sh.rs, [&](int64_t ray, const RayGeom &g) {
-        uint64_t top;
-        int count;
-        search_neighbours<true>(c, g, sh, top, count);
-        const int kk = count < a.K ? count : a.K;
-        const bool mine = l < kk;
-        const int idx = mine ? (int)(uint32_t)top : -1;
-        const float e = mine ? __builtin_sqrtf(__uint_as_float((uint32_t)(top >> 32))) : 0.0f;
-        float w = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
-        if (mine) {
-            w = 1.0f / (e > a.eps_idw ? e : a.eps_idw);
-            const float *col = a.colors + 3 * (int64_t)idx;
-            c0 = w * col[0];
-            c1 = w * col[1];
-            c2 = w * col[2];
+        for (int e = 0; e < 4; ++e) {
+            d[e] = w[e] = c0[e] = c1[e] = c2[e] = 0.0f;
+            if (4 * k16 + e < kk) {
+                d[e] = __builtin_sqrtf(__uint_as_float((uint32_t)(key[e] >> 32)));
+                w[e] = 1.0f / (d[e] > a.eps_idw ? d[e] : a.eps_idw);
+                const float *col = a.colors + 3 * (int64_t)(uint32_t)key[e];
+                c0[e] = w[e] * col[0];
+                c1[e] = w[e] * col[1];
+                c2[e] = w[e] * col[2];
+            }
         }
-        const float ws = wave_sum_f32(w);
-        c0 = wave_sum_f32(c0);
-        c1 = wave_sum_f32(c1);
-        c2 = wave_sum_f32(c2);
-        if (l == 0) {
-            a.rgb[3 * ray + 0] = kk ? c0 / ws : a.bg[0];
-            a.rgb[3 * ray + 1] = kk ? c1 / ws : a.bg[1];
-            a.rgb[3 * ray + 2] = kk ? c2 / ws : a.bg[2];
+        auto row_sum = [](const float(&v)[4]) {
+            float s = (v[0] + v[1]) + (v[2] + v[3]);
+#pragma unroll
+            for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, WAVE);
+            return s;
+        };
+        const float ws = row_sum(w), s0 = row_sum(c0), s1 = row_sum(c1), s2 = row_sum(c2);
+        if (live && k16 == 0) {
+            a.rgb[3 * ray + 0] = kk ? s0 / ws : a.bg[0];
+            a.rgb[3 * ray + 1] = kk ? s1 / ws : a.bg[1];
+            a.rgb[3 * ray + 2] = kk ? s2 / ws : a.bg[2];
             if (a.cnt) a.cnt[ray] = kk;
         }
-        if (a.idx && l < a.K) {
-            a.idx[ray * a.K + l] = idx;
-            a.dist[ray * a.K + l] = e;
+        if (live && a.idx) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = 4 * k16 + e;
+                if (k < a.K) {
+                    a.idx[ray * a.K + k] = k < kk ? (int32_t)(uint32_t)key[e] : -1;
+                    a.dist[ray * a.K + k] = d[e];
+                }
+            }
         }
         lds_sync();
     }, [&](int64_t ray) {
+        const KnpArgs a = phase_arg<KnpArgs>();
         // (one lane) a ray with no point near it: background, no point
         a.rgb[3 * ray + 0] = a.bg[0];
         a.rgb[3 * ray + 1] = a.bg[1];
@@ -69,8 +82,10 @@ k_knp(SearchCtx c, KnpArgs a)
     });
 }
 
-hipError_t launch_knp(const SearchCtx &c, const KnpArgs &a, hipStream_t s)
+hipError_t launch_knp(const SearchCtx &ctx, const KnpArgs &a, hipStream_t s)
 {
+    SearchCtx c = ctx;
+    if (c.chunk <= 0) c.chunk = default_chunk(c);
     const int64_t blocks = banded_grid(c, c.blocks > 0 ? c.blocks : DEFAULT_SEARCH_BLOCKS);
     if (blocks == 0) return hipSuccess;
     k_knp<<<dim3((unsigned)blocks), dim3(WAVE), 0, s>>>(c, a);

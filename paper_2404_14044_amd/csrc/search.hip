@@ -5,22 +5,118 @@
 
 namespace hp {
 
-template <int KT, bool MS>
-__device__ __forceinline__ void search_sample_body(const SearchCtx &c, const SampleOut &o)
+// (one lane) a ray with no point near it: no neighbour, no sample
+__device__ __forceinline__ void put_empty(int64_t ray)
 {
-    __shared__ SearchLds sh;
-    const int l = lane_id();
-    for_each_ray_banded(c, sh.rs, [&](int64_t gray, const RayGeom &g) {
-        const int64_t ray = gray - c.ray0;  // row of the outputs
-        uint64_t top;
-        int count;
-        search_neighbours(c, g, sh, top, count);
-        const int m = count < c.M ? count : c.M;
-        const int64_t rbase = ray * c.S;
+    const SearchCtx c = phase_ctx();
+    const SampleOut o = phase_arg<SampleOut>();
+    o.n_sel[ray] = 0;
+    o.n_nbr[ray] = 0;
+    o.flags[ray] = 0u;
+    o.primary[ray] = -1;
+    if (o.nbr_idx) {
+        for (int i = 0; i < c.M; ++i) {
+            o.nbr_idx[ray * c.M + i] = -1;
+            o.nbr_t[ray * c.M + i] = 0.0f;
+        }
+    }
+}
+
+// Search neighbouring rays together, walk their candidates four rays at a time.
+template <int KT>
+__device__ __forceinline__ void search_sample_body()
+{
+    __shared__ WalkLds sh;
+    int ns = 0;  // slots filled
+    for_each_group_banded<GROUP>(sh.rs, [&](int n, int ray, int rec, bool last) {
+        // (as many of the group as there are slots left, the rest after the walk)
+        while (n > 0) {
+            const int m = min(n, GROUP - ns);
+            lds_sync();
+            if (lane_id() < m) {
+                sh.slot[ns + lane_id()].ray = ray + lane_id();
+                sh.slot[ns + lane_id()].rs = rec + lane_id();
+            }
+            lds_sync();
+            search_group<GROUP, HELD_WALK>(sh.rs, sh.slot, sh.search(), ns, m, WAVE, HELD_WALK);
+            ns += m;
+            n -= m;
+            ray += m;
+            rec += m;
+            if (!(ns == GROUP || (last && n == 0))) continue;
+            const SearchCtx c = phase_ctx();
+            const SampleOut o = phase_arg<SampleOut>();
+            // rows of four values at a time where every row starts on 16 bytes
+            const bool vec = nbr_vec_ok(o.knn_idx, o.knn_dist, c.K);
+            walk_batch<KT>(sh, ns,
+                [&](int rr, int i, int mm, int count, const uint64_t(&key)[4]) {
+                    if (i == 0) {
+                        o.n_nbr[rr] = mm;
+                        o.flags[rr] = count > c.M ? 1u : 0u;
+                    }
+                    if (!o.nbr_idx) return;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if (i + e >= c.M) break;
+                        const int64_t at = (int64_t)rr * c.M + i + e;
+                        o.nbr_idx[at] = i + e < mm ? (int32_t)(uint32_t)key[e] : -1;
+                        o.nbr_t[at] = i + e < mm ? __uint_as_float((uint32_t)(key[e] >> 32)) : 0.0f;
+                    }
+                },
+                [&](int rr, int s, float tj, const uint64_t(&kd)[KT], const float(&dist)[KT], int kc) {
+                    const int64_t row = (int64_t)rr * c.S + s;
+                    o.t[row] = tj;
+                    int32_t *const pi = o.knn_idx + row * c.K;
+                    float *const pd = o.knn_dist + row * c.K;
+#pragma unroll
+                    for (int k0 = 0; k0 < KT; k0 += 4) {
+                        if (k0 >= c.K) break;
+                        int32_t v[4];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) v[k] = k0 + k < kc ? (int32_t)(uint32_t)kd[k0 + k] : -1;
+                        if (vec) {
+                            *reinterpret_cast<int4 *>(pi + k0) = make_int4(v[0], v[1], v[2], v[3]);
+                            *reinterpret_cast<float4 *>(pd + k0) =
+                                make_float4(dist[k0], dist[k0 + 1], dist[k0 + 2], dist[k0 + 3]);
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                if (k0 + k < c.K) {
+                                    pi[k0 + k] = v[k];
+                                    pd[k0 + k] = dist[k0 + k];
+                                }
+                            }
+                        }
+                    }
+                },
+                [&](int rr, int index) { o.primary[rr] = index; },
+                [&](int rr, int nsel) {
+                    o.n_sel[rr] = nsel;
+                    if (nsel == 0) o.primary[rr] = -1;
+                });
+            ns = 0;
+        }
+    }, [&](int64_t ray) { put_empty(ray); });
+}
+
+// The same search with the uniform multi-surface sampler, one ray at a time.
+template <int KT>
+__device__ __forceinline__ void search_ms_body()
+{
+    __shared__ SlabLds sh;
+    for_each_group_banded<1>(sh.rs, [&](int, int ray, int rec, bool) {
+        SlabKeys slab;
+        first_slab(sh, slab, rec);
+        const int count = slab.rest;
+        const RayGeom g = load_ray(sh.rs[rec]);
+        const SearchCtx c = phase_ctx();
+        const SampleOut o = phase_arg<SampleOut>();
+        const int l = lane_id(), m = min(count, c.M);
+        const int64_t rbase = (int64_t)ray * c.S;
         int prim;
         auto emit = [&](int s, int q, float tj, const uint64_t(&kd)[KT], const float(&dq)[KT / 4],
                         int kc) {
-            // the candidate's four lanes share the row: lane q writes k = q, q + 4, ...
+            // the position's four lanes share the row: lane q writes k = q, q + 4, ...
             const int64_t row = rbase + s;
             if (q == 0) o.t[row] = tj;
 #pragma unroll
@@ -33,67 +129,52 @@ __device__ __forceinline__ void search_sample_body(const SearchCtx &c, const Sam
                 }
             }
         };
-        int nsel;
-        if constexpr (MS) nsel = uniform_samples<KT>(c, g, sh, top, count, prim, emit);
-        else nsel = walk_candidates<KT>(c, g, sh, top, m, prim, emit);
-        if (l == 0) {
-            o.n_sel[ray] = nsel;
+        if (o.nbr_idx && l < c.M) {
+            o.nbr_idx[(int64_t)ray * c.M + l] = l < m ? (int)(uint32_t)slab.keys : -1;
+            o.nbr_t[(int64_t)ray * c.M + l] = l < m ? __uint_as_float((uint32_t)(slab.keys >> 32)) : 0.0f;
+        }
+        const int nsel = uniform_samples<KT>(g, sh, slab, prim, emit);
+        if (lane_id() == 0) {
             o.n_nbr[ray] = m;
             o.flags[ray] = (count > c.M) ? 1u : 0u;
+            o.n_sel[ray] = nsel;
             o.primary[ray] = prim;
         }
-        const float tj = __uint_as_float((uint32_t)(top >> 32));
-        const int idxj = (int)(uint32_t)top;
-        if (o.nbr_idx && l < c.M) {
-            o.nbr_idx[ray * c.M + l] = l < m ? idxj : -1;
-            o.nbr_t[ray * c.M + l] = l < m ? tj : 0.0f;
-        }
         lds_sync();
-    }, [&](int64_t gray) {
-        // (one lane) a ray with no point near it: no neighbour, no sample
-        const int64_t ray = gray - c.ray0;
-        o.n_sel[ray] = 0;
-        o.n_nbr[ray] = 0;
-        o.flags[ray] = 0u;
-        o.primary[ray] = -1;
-        if (o.nbr_idx) {
-            for (int i = 0; i < c.M; ++i) {
-                o.nbr_idx[ray * c.M + i] = -1;
-                o.nbr_t[ray * c.M + i] = 0.0f;
-            }
-        }
-    });
+    }, [&](int64_t ray) { put_empty(ray); });
 }
 
-// 6 waves per SIMD where the nearest-neighbour lists are short (80 VGPRs,
-// fewer spills than at 8; with the default grid of many more workgroups
-// than fit at once, 6 measured 3% faster than 8, and 7, 5 or 4 slower).
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(6, 8)))
-k_search_sample_k4(SearchCtx c, SampleOut o) { search_sample_body<4, false>(c, o); }
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(6, 8)))
-k_search_sample_k8(SearchCtx c, SampleOut o) { search_sample_body<8, false>(c, o); }
-// 16-entry lists: 5 waves per SIMD (room view 9% faster than 4, 3 slower)
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(5, 8)))
-k_search_sample_k16(SearchCtx c, SampleOut o) { search_sample_body<16, false>(c, o); }
-__global__ void __launch_bounds__(WAVE) k_search_sample_k32(SearchCtx c, SampleOut o)
+// 4 waves per SIMD (128 VGPRs, no spill with lists of up to 8; the LDS allows
+// 18 one-wave workgroups per CU).  A kernel whose waves own scratch memory is
+// slower to launch waves and slower in all: at 5 waves with spills the room
+// view's 16-entry lists measured 2.78 against 2.55 ms.
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_search_sample_k4(SearchCtx, SampleOut) { search_sample_body<4>(); }
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_search_sample_k8(SearchCtx, SampleOut) { search_sample_body<8>(); }
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_search_sample_k16(SearchCtx, SampleOut) { search_sample_body<16>(); }
+__global__ void __launch_bounds__(WAVE) k_search_sample_k32(SearchCtx, SampleOut)
 {
-    search_sample_body<32, false>(c, o);
+    search_sample_body<32>();
 }
 
 // The same search with the uniform multi-surface sampler.
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(6, 8)))
-k_search_ms_k4(SearchCtx c, SampleOut o) { search_sample_body<4, true>(c, o); }
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(6, 8)))
-k_search_ms_k8(SearchCtx c, SampleOut o) { search_sample_body<8, true>(c, o); }
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_search_ms_k16(SearchCtx c, SampleOut o) { search_sample_body<16, true>(c, o); }
-__global__ void __launch_bounds__(WAVE) k_search_ms_k32(SearchCtx c, SampleOut o)
+k_search_ms_k4(SearchCtx, SampleOut) { search_ms_body<4>(); }
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_search_ms_k8(SearchCtx, SampleOut) { search_ms_body<8>(); }
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_search_ms_k16(SearchCtx, SampleOut) { search_ms_body<16>(); }
+__global__ void __launch_bounds__(WAVE) k_search_ms_k32(SearchCtx, SampleOut)
 {
-    search_sample_body<32, true>(c, o);
+    search_ms_body<32>();
 }
 
-hipError_t launch_search_sample(const SearchCtx &c, const SampleOut &o, int kt, hipStream_t s)
+hipError_t launch_search_sample(const SearchCtx &ctx, const SampleOut &o, int kt, hipStream_t s)
 {
+    SearchCtx c = ctx;
+    if (c.chunk <= 0) c.chunk = default_chunk(c);
     const int64_t blocks = banded_grid(c, c.blocks > 0 ? c.blocks : DEFAULT_SEARCH_BLOCKS);
     if (blocks == 0) return hipSuccess;
     const dim3 grid((unsigned)blocks), block(WAVE);
