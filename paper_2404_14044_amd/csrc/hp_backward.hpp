@@ -7,8 +7,13 @@
 namespace hp {
 
 constexpr int BWD_WAVES = 8;          // waves per workgroup (one workgroup per CU)
-constexpr int BWD_CHUNK = 256;        // samples one wave holds at once
+constexpr int BWD_CHUNK = 64;         // samples one wave holds at once (at least HP_MAX_SAMPLES)
+constexpr int BWD_TAKE = 128;         // samples the rays that a wave takes at a time may have
+constexpr int BWD_QUEUES = 8;         // work counters, a 128-byte line each
+constexpr int BWD_QUEUE_STRIDE = 32;
 constexpr int BWD_MAX_BLOCKS = 256;   // bound on the persistent grid (one gradient slice each)
+
+static_assert(BWD_CHUNK >= HP_MAX_SAMPLES, "a ray's samples are held at once");
 
 struct MlpGrad {
     float *W1, *b1, *W2, *b2, *W3, *b3;
@@ -20,7 +25,7 @@ struct BwdArgs {
     const int32_t *knn_idx;
     const float *knn_dist;
     int64_t n_rays;
-    int32_t K, S, rpw;  // rpw: rays per wave chunk, rpw * S <= BWD_CHUNK
+    int32_t K, S, rpw;  // rpw: rays a wave takes at a time, rpw * S <= BWD_TAKE
     const float *feat;
     MlpWeights w;
     float eps_idw, delta_last;
@@ -28,15 +33,12 @@ struct BwdArgs {
     const float *grad_rgb;
     float *grad_feat;
     float *partial;  // per-workgroup decoder-gradient slices
-    int32_t *queue;  // work counter of one accumulate launch (zeroed before it)
-    const MlpBf16Shared *wimg;  // the BF16 decoder packed per lane (after the counter)
+    int32_t *queue;  // work counters of one accumulate launch (zeroed before it)
 };
 
 // Decoder-gradient slices: one per workgroup of the backward grid, which is
 // at most backward_slices() workgroups for any number of rays, followed by
-// the work counter of the accumulate launches and the BF16 decoder's
-// fragments packed per lane (read by every tile's decode instead of loading
-// and converting the FP32 weights each time).
+// the work counters of the accumulate launches.
 size_t backward_partial_bytes();
 int backward_slices();
 int backward_rays_per_wave(int S);

@@ -1386,9 +1386,11 @@ __device__ __forceinline__ void lane_merge(uint64_t (&x)[R])
 template <int R>
 __device__ __forceinline__ void row_sort(uint64_t (&x)[R])
 {
-    static_assert(R == 4 || R == 8, "four or eight keys per lane");
+    static_assert(R == 2 || R == 4 || R == 8, "two, four or eight keys per lane");
     if constexpr (R == 8) {
         sort8(x);
+    } else if constexpr (R == 2) {
+        kswap(x[0], x[1]);
     } else {
         kswap(x[0], x[1]);
         kswap(x[2], x[3]);
