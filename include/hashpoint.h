@@ -117,10 +117,10 @@ typedef struct hp_camera {
  *  layout: HP_LAYOUT_ROWMAJOR, HP_LAYOUT_TILED or HP_LAYOUT_MORTON (Sec. 3.2
  *      mentions a Z-order arrangement; read here as an order of buckets).
  *  flags: reserved, must be 0.
- *  search_chunk: rays a search workgroup takes at a time, 0 = default (1 to 8 by
- *      the number of rays),
- *      at most 64; search_blocks: search grid (workgroups each taking
- *      chunks of rays in turn), 0 = default (65,536).
+ *  search_chunk: rays a search workgroup takes at a time, 0 = default (1 to 4 by
+ *      the number of rays), at most 64; search_blocks: search grid (waves
+ *      each taking chunks of rays in turn), 0 = default (by the number of
+ *      rays).
  *      Neither changes any result; an autotuner picks them per workload.
  *  radius_mode: HP_RADIUS_*.  In the Eq. 3 modes rho(t) = kappa t with, for
  *      the pixel centre E = (a, b, 1) on the image plane at unit focal

@@ -1,12 +1,21 @@
 // Search, sampling and rendering in one kernel (Sec. 3.2-3.4): the samples of
-// a ray never leave the workgroup.  One wave per ray, persistent over
-// XCD-banded chunks like the forward search: the search and the candidate
-// walk (or the uniform sampler) emit each sample's t and nearest neighbours
-// into LDS, then the wave aggregates the features of its (at most 16)
-// samples as one MFMA tile, decodes them and composites the ray.  Every
-// operation and its order are those of hp_search_sample followed by
+// a ray never leave the workgroup.  Every wave searches and walks groups of
+// rays of its own, as the forward search does, with the samples emitted into
+// its LDS; the samples of the (up to four) rays of one walk are then packed
+// into tiles of 16, aggregated, decoded and composited, as the render does.
+// Every operation and its order are those of hp_search_sample followed by
 // hp_render, so the outputs are identical; what is saved is the sample
-// arrays' round trip through HBM and a launch.
+// arrays' round trip through memory and a launch.
+//
+// Bound by the latency and the instructions of the search.  The decoder's
+// operands are packed once per workgroup into the LDS and read by its waves
+// when a tile needs them (as in the shared render): kept in a wave's registers
+// beside the search's state, and loaded again for every ray, they held the
+// kernel to two waves per SIMD, and a tile per ray was a fifth full.  One
+// workgroup per CU, its waves dealing out its rays among themselves: a second
+// workgroup to replace it, let alone four, leaves the CU idle while the first
+// drains (425, 507, 540 us).  Frame of 640k rays of the object, BF16: 1,518 us
+// with one-wave workgroups, 425 here (the separate calls 317 + 188).
 #include <type_traits>
 
 #include "hp_kernels.hpp"
@@ -15,49 +24,85 @@
 
 namespace hp {
 
-constexpr int FUSED_S = 16;  // samples per ray the fused kernel holds (one tile)
+constexpr int FUSED_S = 16;  // samples per ray the fused kernel holds
 
-// (a wave's LDS: the search's, and the samples of the rays of one walk; the
-// multi-surface sampler serves one ray at a time)
-template <int KT, bool MS>
-struct FusedLds {
-    typename std::conditional<MS, SlabLds, WalkLds>::type w;
-    static constexpr int RAYS = MS ? 1 : GROUP;
+// The samples of RAYS rays: what the walk (or the uniform sampler) emits.
+template <int RAYS, int KT>
+struct FusedSamples {
     float t[RAYS][FUSED_S];
     int32_t idx[RAYS][FUSED_S][KT];
-    float dist[RAYS][FUSED_S][KT];
+    float w[RAYS][FUSED_S][KT];  // inverse-distance weights, not normalised
     int32_t ray[RAYS], n[RAYS];
-    float4 out[FUSED_S];  // (sigmoid rgb, softplus sigma) per sample
 };
 
-// Aggregate, decode and composite the n samples held in slot k (as the render).
-template <int KT, int PREC, bool MS>
-__device__ __forceinline__ void fused_render(FusedLds<KT, MS> &sh,
-                                             int k, int64_t ray, int n)
+// A wave's LDS.  The walk's lists are dead when its samples are decoded, so
+// the decoded samples take their place.
+template <int KT>
+struct FusedWalkLists : WalkLists {
+    FusedSamples<GROUP, KT> smp;
+};
+
+template <int KT, bool MS>
+struct FusedLds;
+
+template <int KT>
+struct FusedLds<KT, false> : WalkLdsOf<FusedWalkLists<KT>> {
+    static constexpr int RAYS = GROUP;
+    __device__ __forceinline__ FusedSamples<GROUP, KT> &samples() { return this->lists().smp; }
+    __device__ __forceinline__ float4 *out() { return this->lists().p; }
+    static_assert(sizeof(WalkLists) >= GROUP * FUSED_S * sizeof(float4), "decoded samples exceed the lists");
+};
+
+template <int KT>
+struct FusedLds<KT, true> : SlabLds {
+    static constexpr int RAYS = 1;
+    FusedSamples<1, KT> smp;
+    float4 dec[FUSED_S];
+    __device__ __forceinline__ FusedSamples<1, KT> &samples() { return smp; }
+    __device__ __forceinline__ float4 *out() { return dec; }
+};
+
+// Aggregate, decode and composite the samples of the first ns rays held.
+template <int KT, int PREC, bool MS, typename Image>
+__device__ __forceinline__ void fused_render(FusedLds<KT, MS> &sh, const Image &img, int ns)
 {
     const SearchCtx c = phase_ctx();
     const FusedArgs a = phase_arg<FusedArgs>();
+    constexpr int RAYS = FusedLds<KT, MS>::RAYS;
     const int l = phase_lane_id();
     const int r16 = l & 15, q = l >> 4;
-    if (n > 0) {
-        // aggregation (lane: sample r16, features 8 q .. 8 q + 7), as the render
+    auto &smp = sh.samples();
+    float4 *const out = sh.out();
+    lds_sync();
+    int pre[RAYS + 1];  // first sample of each ray
+    pre[0] = 0;
+#pragma unroll
+    for (int k = 0; k < RAYS; ++k) pre[k + 1] = pre[k] + (k < ns ? uniform_i32(smp.n[k]) : 0);
+    const int total = pre[RAYS];
+    for (int s0 = 0; s0 < total; s0 += 16) {
+        const int sidx = s0 + r16;
+        const bool valid = sidx < total;
+        // aggregation (lane: sample r16, features 8 q .. 8 q + 7): neighbours
+        // four at a time, summed in order
         float f[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] = 0.0f;
-        if (r16 < n) {
-            // neighbours four at a time, summed in order (as the render)
+        if (valid) {
+            int k = 0, s = sidx;
+#pragma unroll
+            for (int j = 1; j < RAYS; ++j) {
+                k = sidx >= pre[j] ? j : k;
+                s = sidx >= pre[j] ? sidx - pre[j] : s;
+            }
+            const int32_t *const ki = smp.idx[k][s];
+            const float *const kw = smp.w[k][s];
             float wsum = 0.0f;
             for (int k0 = 0; k0 < c.K; k0 += 4) {
-                int idx[4];
-                float w[4];
+                const int4 iv = *reinterpret_cast<const int4 *>(ki + k0);
+                const float4 wv = *reinterpret_cast<const float4 *>(kw + k0);
+                const int idx[4] = {iv.x, iv.y, iv.z, iv.w};
+                const float w[4] = {wv.x, wv.y, wv.z, wv.w};
                 float4 x0[4], x1[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const bool in = k0 + j < c.K;
-                    idx[j] = in ? sh.idx[k][r16][k0 + j] : -1;
-                    const float d = in ? sh.dist[k][r16][k0 + j] : 1.0f;
-                    w[j] = 1.0f / (d > a.eps_idw ? d : a.eps_idw);
-                }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     if (idx[j] >= 0) {
@@ -88,29 +133,31 @@ __device__ __forceinline__ void fused_render(FusedLds<KT, MS> &sh,
             for (int e = 0; e < 8; ++e) f[e] *= inv;
         }
         f32x4 o;
-        // load the weights here (cache hits) rather than keep them live
-        // across the search
         __asm__ volatile("" ::: "memory");
-        if constexpr (PREC == HP_BF16) {
-            MlpBf16 mlp;
-            load_mlp_bf16(a.w, mlp);
-            o = decode_bf16(mlp, f);
-        } else {
-            MlpF32 mlp;
-            load_mlp_f32(a.w, mlp);
-            o = decode_f32(mlp, f);
-        }
-        if (q == 0 && r16 < n)
-            sh.out[r16] = make_float4(sigmoid_f(o[0]), sigmoid_f(o[1]), sigmoid_f(o[2]),
-                                      softplus_f(o[3]));
+        if constexpr (PREC == HP_BF16) o = decode_bf16(img, f);
+        else o = decode_f32(img, f);
+        // the activations on all of the sample's lanes, one output each
+        if (q == 0 && valid) out[sidx] = make_float4(o[0], o[1], o[2], o[3]);
         lds_sync();
+        if (valid) {
+            float *const v = reinterpret_cast<float *>(&out[sidx]) + q;
+            const float x = *v;
+            *v = q < 3 ? sigmoid_f(x) : softplus_f(x);
+        }
     }
-    if (l == 0) {
+    lds_sync();
+    if (l < ns) {
+        // lane k composites ray k
+        const int n = smp.n[l];
+        const int64_t ray = smp.ray[l];
+        int base = 0;
+#pragma unroll
+        for (int k = 1; k < RAYS; ++k) base = l >= k ? pre[k] : base;
         float T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f, dep = 0.0f, ws = 0.0f;
         for (int s = 0; s < n; ++s) {
-            const float4 v = sh.out[s];
-            const float t = sh.t[k][s];
-            const float delta = (s + 1 < n) ? sh.t[k][s + 1] - t : a.delta_last;
+            const float4 v = out[base + s];
+            const float t = smp.t[l][s];
+            const float delta = (s + 1 < n) ? smp.t[l][s + 1] - t : a.delta_last;
             const float e = expf(-v.w * delta);
             const float w = T * (1.0f - e);
             cr = fma_rn(w, v.x, cr);
@@ -143,43 +190,74 @@ __device__ __forceinline__ void fused_empty(int64_t ray)
     if (a.n_sel) a.n_sel[ray] = 0;
 }
 
+template <int PREC>
+using FusedImage = typename std::conditional<PREC == HP_BF16, MlpBf16Shared, MlpF32Shared>::type;
+
+// Waves per workgroup, one of which fills a CU: as many as the LDS holds beside
+// the decoder, up to 4 per SIMD (128 VGPRs; lists of 16 need more than that: 3).
 template <int KT, int PREC, bool MS>
-__device__ __forceinline__ void fused_body()
+constexpr int fused_waves()
 {
-    __shared__ FusedLds<KT, MS> sh;
+    const int fit = (int)((163840 - 16 - sizeof(FusedImage<PREC>)) / sizeof(FusedLds<KT, MS>));
+    const int most = KT <= 8 ? 16 : 12;
+    return fit < most ? fit : most;
+}
+
+template <int KT, int PREC, bool MS>
+__global__ void __launch_bounds__((WAVE * fused_waves<KT, PREC, MS>())) k_fused(SearchCtx, FusedArgs)
+{
+    constexpr int NW = fused_waves<KT, PREC, MS>();
+    __shared__ FusedImage<PREC> img;
+    __shared__ FusedLds<KT, MS> waves[NW];
+    __shared__ int take;
+    if (threadIdx.x == 0) take = 0;
+    {
+        const FusedArgs a = phase_arg<FusedArgs>();
+        const int w = threadIdx.x / WAVE;
+        if constexpr (PREC == HP_BF16) store_mlp_bf16_shared(a.w, img, w, NW);
+        else store_mlp_f32_shared(a.w, img, w, NW);
+    }
+    __syncthreads();
+    FusedLds<KT, MS> &sh = waves[threadIdx.x / WAVE];
+    auto &smp = sh.samples();
     auto empty = [&](int64_t ray) { fused_empty(ray); };
+    auto weight = [](float d, float eps) { return 1.0f / (d > eps ? d : eps); };
     if constexpr (MS) {
-        for_each_group_banded<1>(sh.w.rs, [&](int, int ray, int rec, bool) {
+        for_each_group_banded<1, NW>(sh.rs, &take, [&](int, int ray, int rec, bool) {
             SlabKeys slab;
-            first_slab(sh.w, slab, rec);
-            const RayGeom g = load_ray(sh.w.rs[rec]);
+            first_slab(sh, slab, rec);
+            const RayGeom g = load_ray(sh.rs[rec]);
+            const float eps = phase_arg<FusedArgs>().eps_idw;
             int prim;
-            const int n = uniform_samples<KT>(g, sh.w, slab, prim,
+            const int n = uniform_samples<KT>(g, sh, slab, prim,
                 [&](int s, int q, float tj, const uint64_t(&kd)[KT], const float(&dq)[KT / 4], int kc) {
-                    if (q == 0) sh.t[0][s] = tj;
+                    if (q == 0) smp.t[0][s] = tj;
 #pragma unroll
                     for (int e = 0; e < KT / 4; ++e) {
                         const int k = 4 * e + q;
                         const bool v = k < kc;  // (kc <= K)
-                        sh.idx[0][s][k] = v ? (int32_t)(uint32_t)quad_entry<KT>(kd, e) : -1;
-                        sh.dist[0][s][k] = v ? dq[e] : 0.0f;
+                        smp.idx[0][s][k] = v ? (int32_t)(uint32_t)quad_entry<KT>(kd, e) : -1;
+                        smp.w[0][s][k] = weight(v ? dq[e] : 0.0f, eps);
                     }
                 });
-            lds_sync();
-            fused_render<KT, PREC, MS>(sh, 0, ray, n);
+            if (lane_id() == 0) {
+                smp.ray[0] = ray;
+                smp.n[0] = n;
+            }
+            fused_render<KT, PREC, MS>(sh, img, 1);
         }, empty);
     } else {
         int ns = 0;  // slots filled
-        for_each_group_banded<GROUP>(sh.w.rs, [&](int n, int ray, int rec, bool last) {
+        for_each_group_banded<GROUP, NW>(sh.rs, &take, [&](int n, int ray, int rec, bool last) {
             while (n > 0) {
                 const int m = min(n, GROUP - ns);
                 lds_sync();
                 if (lane_id() < m) {
-                    sh.w.slot[ns + lane_id()].ray = ray + lane_id();
-                    sh.w.slot[ns + lane_id()].rs = rec + lane_id();
+                    sh.slot[ns + lane_id()].ray = ray + lane_id();
+                    sh.slot[ns + lane_id()].rs = rec + lane_id();
                 }
                 lds_sync();
-                search_group<GROUP, HELD_WALK>(sh.w.rs, sh.w.slot, sh.w.search(), ns, m, WAVE, HELD_WALK);
+                search_group<GROUP, HELD_WALK>(sh.rs, sh.slot, sh.search(), ns, m, WAVE, HELD_WALK);
                 ns += m;
                 n -= m;
                 ray += m;
@@ -187,64 +265,59 @@ __device__ __forceinline__ void fused_body()
                 if (!(ns == GROUP || (last && n == 0))) continue;
                 // (a ray's slot is its lane's row of the walk)
                 const int slot = lane_id() >> 4;
-                walk_batch<KT>(sh.w, ns, [](int, int, int, int, const uint64_t(&)[4]) {},
+                const float eps = phase_arg<FusedArgs>().eps_idw;
+                walk_batch<KT>(sh, ns, [](int, int, int, int, const uint64_t(&)[4]) {},
                     [&](int, int s, float tj, const uint64_t(&kd)[KT], const float(&dist)[KT], int kc) {
-                        sh.t[slot][s] = tj;
+                        smp.t[slot][s] = tj;
 #pragma unroll
                         for (int k = 0; k < KT; ++k) {
-                            sh.idx[slot][s][k] = k < kc ? (int32_t)(uint32_t)kd[k] : -1;
-                            sh.dist[slot][s][k] = dist[k];
+                            smp.idx[slot][s][k] = k < kc ? (int32_t)(uint32_t)kd[k] : -1;
+                            smp.w[slot][s][k] = weight(dist[k], eps);
                         }
                     },
                     [](int, int) {},
                     [&](int rr, int nsel) {
-                        sh.ray[slot] = rr;
-                        sh.n[slot] = nsel;
+                        smp.ray[slot] = rr;
+                        smp.n[slot] = nsel;
                     });
-                for (int k = 0; k < ns; ++k)
-                    fused_render<KT, PREC, MS>(sh, k, uniform_i32(sh.ray[k]), uniform_i32(sh.n[k]));
+                fused_render<KT, PREC, MS>(sh, img, ns);
                 ns = 0;
             }
         }, empty);
     }
 }
 
-// The decoder's weights live in registers (as in the render), which with the
-// search's state needs about 240 VGPRs: 2 waves per SIMD.
-template <int KT, int PREC, bool MS>
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_fused(SearchCtx, FusedArgs)
-{
-    fused_body<KT, PREC, MS>();
-}
-
 int fused_max_samples() { return FUSED_S; }
 
-template <int KT, int PREC>
-static void launch_fused_kp(const SearchCtx &c, const FusedArgs &a, dim3 grid, hipStream_t s)
+template <int KT, int PREC, bool MS>
+static void launch_fused_kpm(const SearchCtx &c, const FusedArgs &a, hipStream_t s)
 {
-    if (c.sampler == HP_SAMPLER_MS) k_fused<KT, PREC, true><<<grid, dim3(WAVE), 0, s>>>(c, a);
-    else k_fused<KT, PREC, false><<<grid, dim3(WAVE), 0, s>>>(c, a);
+    constexpr int NW = fused_waves<KT, PREC, MS>();
+    const int64_t blocks = banded_grid(c, c.blocks > 0 ? (c.blocks + NW - 1) / NW : CU_BLOCKS);
+    if (blocks == 0) return;
+    k_fused<KT, PREC, MS><<<dim3((unsigned)blocks), dim3(WAVE * NW), 0, s>>>(c, a);
 }
 
 template <int KT>
-static void launch_fused_k(const SearchCtx &c, const FusedArgs &a, int precision, dim3 grid,
-                           hipStream_t s)
+static void launch_fused_k(const SearchCtx &c, const FusedArgs &a, int precision, hipStream_t s)
 {
-    if (precision == HP_BF16) launch_fused_kp<KT, HP_BF16>(c, a, grid, s);
-    else launch_fused_kp<KT, HP_FP32>(c, a, grid, s);
+    const bool ms = c.sampler == HP_SAMPLER_MS;
+    if (precision == HP_BF16) {
+        if (ms) launch_fused_kpm<KT, HP_BF16, true>(c, a, s);
+        else launch_fused_kpm<KT, HP_BF16, false>(c, a, s);
+    } else {
+        if (ms) launch_fused_kpm<KT, HP_FP32, true>(c, a, s);
+        else launch_fused_kpm<KT, HP_FP32, false>(c, a, s);
+    }
 }
 
 hipError_t launch_fused(const SearchCtx &ctx, const FusedArgs &a, int kt, int precision, hipStream_t s)
 {
     SearchCtx c = ctx;
-    if (c.chunk <= 0) c.chunk = default_chunk(c);
-    const int64_t blocks = banded_grid(c, c.blocks > 0 ? c.blocks : DEFAULT_SEARCH_BLOCKS);
-    if (blocks == 0) return hipSuccess;
-    const dim3 grid((unsigned)blocks);
-    if (kt == 4) launch_fused_k<4>(c, a, precision, grid, s);
-    else if (kt == 8) launch_fused_k<8>(c, a, precision, grid, s);
-    else launch_fused_k<16>(c, a, precision, grid, s);
+    if (c.chunk <= 0) c.chunk = default_chunk(c, SEARCH_FUSED);
+    if (kt == 4) launch_fused_k<4>(c, a, precision, s);
+    else if (kt == 8) launch_fused_k<8>(c, a, precision, s);
+    else launch_fused_k<16>(c, a, precision, s);
     return hipGetLastError();
 }
 

@@ -156,23 +156,28 @@ struct WalkLists {
 };
 
 // Search, then walk: the two never hold data at the same time (the walk reads
-// the keys into registers before it writes its lists).
-struct WalkLds {
+// the keys into registers before it writes its lists).  LISTS begins with a
+// WalkLists and may hold more that lives as long.
+template <typename LISTS>
+struct WalkLdsOf {
     RayGeom rs[RS_CAP];
     RaySlot slot[GROUP];
-    alignas(16) unsigned char mem[sizeof(SearchScratch<GROUP, HELD_WALK>) > sizeof(WalkLists) ? sizeof(SearchScratch<GROUP, HELD_WALK>)
-                                                                                   : sizeof(WalkLists)];
+    alignas(16) unsigned char mem[sizeof(SearchScratch<GROUP, HELD_WALK>) > sizeof(LISTS)
+                                      ? sizeof(SearchScratch<GROUP, HELD_WALK>)
+                                      : sizeof(LISTS)];
 
     __device__ __forceinline__ SearchScratch<GROUP, HELD_WALK> &search()
     {
         return *reinterpret_cast<SearchScratch<GROUP, HELD_WALK> *>(mem);
     }
-    __device__ __forceinline__ WalkLists &lists() { return *reinterpret_cast<WalkLists *>(mem); }
+    __device__ __forceinline__ LISTS &lists() { return *reinterpret_cast<LISTS *>(mem); }
 };
+using WalkLds = WalkLdsOf<WalkLists>;
 // (LDS is granted in pieces of 1,280 B: eight of them let 16 one-wave
 // workgroups share a CU's 160 KB)
 static_assert(sizeof(WalkLds) <= 10240, "walk LDS above 10240 B costs occupancy");
 
+// K-NP: the search alone.
 struct KnpLds {
     RayGeom rs[RS_CAP];
     RaySlot slot[GROUP];
@@ -200,35 +205,52 @@ static_assert(sizeof(SlabLds) <= 10240, "slab LDS above 10240 B costs occupancy"
 // 0.534 with 800; room view 3.09, 2.83, 2.81, 2.81 ms).
 constexpr int64_t BAND_RAYS = 1600;
 
-// Default grid of the search launches: 65,536 one-wave workgroups (on the
-// object view, 640k rays, 2.4 chunks of 4 rays each), eight times what the
-// GPU keeps resident, so workgroups that drew empty chunks are replaced as
-// they finish (measured: 8,192 resident-sized persistent workgroups
-// 0.631 ms, 65,536 0.56 ms; room view 4.04 vs 3.69 ms; one workgroup per
-// chunk 0.58 / 3.91 ms).
-constexpr int64_t DEFAULT_SEARCH_BLOCKS = 65536;
+// Two ways to share a launch's rays out, by their number.
+// Up to DEALT_RAYS, and for the multi-surface sampler (whose rays are each
+// long): one-wave workgroups, up to WAVE_BLOCKS of them, eight times what the
+// GPU keeps resident, so that the hardware replaces those that drew little as
+// they finish.
+// Above: one workgroup per CU, as many waves as fit, which deal their share
+// out among themselves as they go (for_each_group_banded): nothing is launched
+// twice and a CU's waves end together.  The shares of the CUs are fixed, which
+// costs more the fewer rays there are (us, one-wave workgroups / dealt: frame
+// of 640k rays of the object 588 / 554, of 762k rays of the room 2508 / 2464,
+// K-NP of 640k rays 246 / 234, search of 307k rays 389 / 386, of 160k 146 / 156,
+// of 65k 99 / 126, of 16k 106 / 134).
+constexpr int64_t WAVE_BLOCKS = 65536, CU_BLOCKS = 256, DEALT_RAYS = 262144;
+
+inline bool dealt(const SearchCtx &c) { return c.blocks <= 0 && c.n_rays > DEALT_RAYS; }
 
 // Rays per work chunk where the caller names none.  Neighbouring rays are
-// searched together, so a chunk of four or more is the cheapest by ray; a
-// launch of few rays leaves most of the GPU idle that way and is better split
-// further (us by rays per chunk, 1 / 2 / 4 / 8, object cloud of 758k points:
-// 2,304 rays 61 / 116 / 227 / 424; 16,384 rays 90 / 93 / 223 / 362; 65,536 rays
-// 146 / 110 / 126 / 173; 640,000 rays 690 / 493 / 414 / 403; room of 1.3M points:
-// 4,096 rays 95 / 146 / 210 / 312; 147,456 rays 626 / 510 / 338 / 297).
-// The multi-surface sampler takes its rays one at a time, each for long.
-inline int32_t default_chunk(const SearchCtx &c)
+// searched together, so a chunk of four is the cheapest by ray; a launch of few
+// rays leaves most of the GPU idle that way, or waiting for the few waves that
+// drew four crowded rays, and is better split further (us by rays per chunk
+// 1 / 2 / 4; object cloud of 1M points, squares of 64, 192, 256, 350 and 500
+// pixels: search 105 / - / 227, 143 / 110 / 145, 176 / 116 / 102, 251 / 161 / 118,
+// 442 / 317 / 241; K-NP 55 / - / -, 77 / 72 / 284, 101 / 78 / 99, 136 / 90 / 79,
+// 450 pixels 172 / 130 / 102; search and render in one, whose CUs' shares are
+// fixed, 119 / 138 / 191, 149 / 187 / 215, 180 / 174 / 247, 299 / 252 / 250).
+// The multi-surface sampler takes its rays one at a time, each for long
+// (640k rays, 400 positions 2268 / 2486 / 3271; 160k rays 795 / 1309 / 2129).
+enum SearchKind { SEARCH_WALK, SEARCH_KNP, SEARCH_FUSED };
+
+inline int32_t default_chunk(const SearchCtx &c, SearchKind kind)
 {
-    return c.n_rays <= 6144 ? 1 : c.n_rays <= 32768 ? 2 : c.n_rays <= 262144 || c.sampler == HP_SAMPLER_MS ? 4 : 8;
+    if (c.sampler == HP_SAMPLER_MS && kind != SEARCH_KNP) return 1;
+    const int64_t one = kind == SEARCH_FUSED ? 65536 : 6144;
+    const int64_t two = kind == SEARCH_FUSED ? 196608 : kind == SEARCH_KNP ? 65536 : 49152;
+    return c.n_rays <= one ? 1 : c.n_rays <= two ? 2 : 4;
 }
 
-// Grid for the banded launches: at most `cap` workgroups, a multiple of 8.
-inline int64_t banded_grid(const SearchCtx &c, int64_t cap)
+// Grid of a search launch: at most `most` workgroups, a multiple of 8.
+inline int64_t banded_grid(const SearchCtx &c, int64_t most)
 {
     const int64_t chunks = (c.n_rays + c.chunk - 1) / c.chunk;
-    int64_t blocks = chunks < cap ? chunks : cap;
+    const int64_t blocks = chunks < most ? chunks : most;
     if (blocks == 0) return 0;
     return blocks < 8 ? 8 : (blocks & ~(int64_t)7);
 }
+inline int64_t wave_grid(const SearchCtx &c) { return banded_grid(c, c.blocks > 0 ? c.blocks : WAVE_BLOCKS); }
 
 // Search radius of a ray at parameter t.
 __device__ __forceinline__ float rho_at(const SearchCtx &c, const RayGeom &g, float t)
@@ -587,11 +609,10 @@ __device__ __forceinline__ RayGeom load_ray(const RayGeom &src)
     return g;
 }
 
-// Persistent iteration over the rays of a launch, one ray at a time per
-// workgroup, body(ray, geometry).  Workgroups take chunks of c.chunk
-// consecutive rays (neighbouring pixels share table buckets).  They are dealt
-// to the eight XCDs round-robin (workgroup b runs on XCD b % 8), each with its
-// own L2, so the chunks are grouped into bands of BAND_RAYS consecutive rays
+// Persistent iteration over the rays of a launch.  Workgroups take chunks of
+// c.chunk consecutive rays (neighbouring pixels share table buckets).  They are
+// dealt to the eight XCDs round-robin (workgroup b runs on XCD b % 8), each with
+// its own L2, so the chunks are grouped into bands of BAND_RAYS consecutive rays
 // and XCD x takes bands x, x + 8, ...: the rays one XCD's workgroups search at
 // a time are then neighbours and share that L2's table lines.  Within its
 // bands an XCD's workgroups stride by their number, so each still sees a mix
@@ -607,8 +628,12 @@ __device__ __forceinline__ RayGeom load_ray(const RayGeom &src)
 // pixels at a time: their number, the first one's number (rays numbered from
 // the launch's first one, which is their row in the outputs) and its record
 // (the others' follow), and whether this pass ends with them.
-template <int MAXG, typename Groups, typename Empty>
-__device__ __forceinline__ void for_each_group_banded(RayGeom *rs, Groups groups, Empty empty)
+// The NW waves of a workgroup take its chunks as they come, by the counter
+// `take` in its LDS (zero at first): up to four at a time, fewer towards the
+// end (measured on the frames above, search and render in one: 569 us with a
+// fixed deal, 467 with passes taken as they come, 425 with the last ones short).
+template <int MAXG, int NW, typename Groups, typename Empty>
+__device__ __forceinline__ void for_each_group_banded(RayGeom *rs, int *take, Groups groups, Empty empty)
 {
     const SearchCtx cl = phase_ctx();
     // (chunk, band and slot numbers in 32 bits: a launch has fewer than 2^31
@@ -634,16 +659,28 @@ __device__ __forceinline__ void for_each_group_banded(RayGeom *rs, Groups groups
         r0 = ch * chunk;
         n = (int)min(chunk, n_rays - r0);
     };
-    // four chunks per set-up pass (the chunks themselves stay small, for balance)
-    for (uint32_t li = slot; li < my_chunks; li += 4 * n_slots) {
-        const SearchCtx c = phase_ctx();
+    // its share of them, in passes of up to four (the chunks themselves stay
+    // small, for balance)
+    const uint32_t mine = slot < my_chunks ? (my_chunks - slot + n_slots - 1) / n_slots : 0;
+    for (uint32_t at = 0;;) {
+        uint32_t per = 4;
         const int l = phase_lane_id();
+        if constexpr (NW > 1) {
+            per = min(max((mine - at) / (2 * NW), 1u), 4u);
+            int j = 0;
+            if (l == 0) j = atomicAdd(take, (int)per);
+            at = (uint32_t)uniform_i32(j);
+        }
+        if (at >= mine) break;
+        const uint32_t li = slot + at * n_slots;
+        if constexpr (NW == 1) at += per;
+        const SearchCtx c = phase_ctx();
         uint32_t ra, rb, rc, rd;
         int na, nb, nc, nd;
         chunk_rays(li, ra, na);
-        chunk_rays(li + n_slots, rb, nb);
-        chunk_rays(li + 2 * n_slots, rc, nc);
-        chunk_rays(li + 3 * n_slots, rd, nd);
+        chunk_rays(per > 1 ? li + n_slots : ~0u, rb, nb);
+        chunk_rays(per > 2 ? li + 2 * n_slots : ~0u, rc, nc);
+        chunk_rays(per > 3 ? li + 3 * n_slots : ~0u, rd, nd);
         const int nab = na + nb, nabc = nab + nc, ntot = nabc + nd;
         auto ray_at = [&](int i) -> int64_t {
             const uint32_t r = i < na ? ra + i : i < nab ? rb + (i - na) : i < nabc ? rc + (i - nab) : rd + (i - nabc);
@@ -1513,8 +1550,8 @@ __device__ __forceinline__ void row_sorted_keys(uint64_t *pend, int held, int mo
 // upper half is KEY_NONE's), their distances and their number kc among the
 // first K; first(ray, index) on the lane of a ray's first sample, and
 // ends(ray, n) on a ray's first lane with its sample count.
-template <int KT, typename Lists, typename Emit, typename First, typename Ends>
-__device__ __forceinline__ void walk_batch(WalkLds &sh, int ns, Lists lists, Emit emit, First first, Ends ends)
+template <int KT, typename Lds, typename Lists, typename Emit, typename First, typename Ends>
+__device__ __forceinline__ void walk_batch(Lds &sh, int ns, Lists lists, Emit emit, First first, Ends ends)
 {
     const SearchCtx c = phase_ctx();
     const int l = phase_lane_id(), r = l >> 4, k16 = l & 15;

@@ -12,11 +12,18 @@
 
 namespace hp {
 
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_knp(SearchCtx, KnpArgs)
+constexpr int KNP_WAVES = 16;  // per workgroup that fills a CU
+
+template <int NW>
+
+__global__ void __launch_bounds__(WAVE *NW) __attribute__((amdgpu_waves_per_eu(4, 8))) k_knp(SearchCtx, KnpArgs)
 {
-    __shared__ KnpLds sh;
-    for_each_group_banded<GROUP>(sh.rs, [&](int n, int ray0, int rec, bool) {
+    __shared__ KnpLds waves[NW];
+    __shared__ int take;
+    if (threadIdx.x == 0) take = 0;
+    __syncthreads();
+    KnpLds &sh = waves[threadIdx.x / WAVE];
+    for_each_group_banded<GROUP, NW>(sh.rs, &take, [&](int n, int ray0, int rec, bool) {
         lds_sync();
         if (lane_id() < n) sh.slot[lane_id()].rs = rec + lane_id();
         lds_sync();
@@ -85,10 +92,11 @@ k_knp(SearchCtx, KnpArgs)
 hipError_t launch_knp(const SearchCtx &ctx, const KnpArgs &a, hipStream_t s)
 {
     SearchCtx c = ctx;
-    if (c.chunk <= 0) c.chunk = default_chunk(c);
-    const int64_t blocks = banded_grid(c, c.blocks > 0 ? c.blocks : DEFAULT_SEARCH_BLOCKS);
+    if (c.chunk <= 0) c.chunk = default_chunk(c, SEARCH_KNP);
+    const int64_t blocks = dealt(c) ? banded_grid(c, CU_BLOCKS) : wave_grid(c);
     if (blocks == 0) return hipSuccess;
-    k_knp<<<dim3((unsigned)blocks), dim3(WAVE), 0, s>>>(c, a);
+    if (dealt(c)) k_knp<KNP_WAVES><<<dim3((unsigned)blocks), dim3(WAVE * KNP_WAVES), 0, s>>>(c, a);
+    else k_knp<1><<<dim3((unsigned)blocks), dim3(WAVE), 0, s>>>(c, a);
     return hipGetLastError();
 }
 

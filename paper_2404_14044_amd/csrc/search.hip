@@ -1,5 +1,4 @@
-// Forward search + sampling kernel: one 64-lane workgroup per ray, persistent
-// over XCD-banded chunks of rays (for_each_ray_banded).
+// Forward search + sampling kernels: waves over XCD-banded chunks of rays.
 #include "hp_kernels.hpp"
 #include "hp_search.hpp"
 
@@ -23,12 +22,16 @@ __device__ __forceinline__ void put_empty(int64_t ray)
 }
 
 // Search neighbouring rays together, walk their candidates four rays at a time.
-template <int KT>
+template <int KT, int NW>
 __device__ __forceinline__ void search_sample_body()
 {
-    __shared__ WalkLds sh;
+    __shared__ WalkLds waves[NW];
+    __shared__ int take;
+    if (threadIdx.x == 0) take = 0;
+    __syncthreads();
+    WalkLds &sh = waves[threadIdx.x / WAVE];
     int ns = 0;  // slots filled
-    for_each_group_banded<GROUP>(sh.rs, [&](int n, int ray, int rec, bool last) {
+    for_each_group_banded<GROUP, NW>(sh.rs, &take, [&](int n, int ray, int rec, bool last) {
         // (as many of the group as there are slots left, the rest after the walk)
         while (n > 0) {
             const int m = min(n, GROUP - ns);
@@ -104,7 +107,7 @@ template <int KT>
 __device__ __forceinline__ void search_ms_body()
 {
     __shared__ SlabLds sh;
-    for_each_group_banded<1>(sh.rs, [&](int, int ray, int rec, bool) {
+    for_each_group_banded<1, 1>(sh.rs, nullptr, [&](int, int ray, int rec, bool) {
         SlabKeys slab;
         first_slab(sh, slab, rec);
         const int count = slab.rest;
@@ -144,54 +147,50 @@ __device__ __forceinline__ void search_ms_body()
     }, [&](int64_t ray) { put_empty(ray); });
 }
 
-// 4 waves per SIMD (128 VGPRs, no spill with lists of up to 8; the LDS allows
-// 18 one-wave workgroups per CU).  A kernel whose waves own scratch memory is
-// slower to launch waves and slower in all: at 5 waves with spills the room
-// view's 16-entry lists measured 2.78 against 2.55 ms.
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_search_sample_k4(SearchCtx, SampleOut) { search_sample_body<4>(); }
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_search_sample_k8(SearchCtx, SampleOut) { search_sample_body<8>(); }
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_search_sample_k16(SearchCtx, SampleOut) { search_sample_body<16>(); }
-__global__ void __launch_bounds__(WAVE) k_search_sample_k32(SearchCtx, SampleOut)
+// 4 waves per SIMD (128 VGPRs, no spill with lists of up to 8), 2 with lists
+// of 32.  A kernel whose waves own scratch memory is slower to launch waves and
+// slower in all: at 5 waves with spills the room view's 16-entry lists measured
+// 2.78 against 2.55 ms.
+constexpr int search_waves(int kt) { return kt <= 16 ? 16 : 8; }  // per workgroup that fills a CU
+
+template <int KT, int NW>
+__global__ void __launch_bounds__(WAVE *NW) __attribute__((amdgpu_waves_per_eu(KT <= 16 ? 4 : 2, 8)))
+k_search_sample(SearchCtx, SampleOut)
 {
-    search_sample_body<32>();
+    search_sample_body<KT, NW>();
 }
 
-// The same search with the uniform multi-surface sampler.
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_search_ms_k4(SearchCtx, SampleOut) { search_ms_body<4>(); }
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_search_ms_k8(SearchCtx, SampleOut) { search_ms_body<8>(); }
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_search_ms_k16(SearchCtx, SampleOut) { search_ms_body<16>(); }
-__global__ void __launch_bounds__(WAVE) k_search_ms_k32(SearchCtx, SampleOut)
+template <int KT>
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(KT <= 16 ? 4 : 2, 8))) k_search_ms(SearchCtx, SampleOut)
 {
-    search_ms_body<32>();
+    search_ms_body<KT>();
+}
+
+template <int KT>
+static void launch_search_k(const SearchCtx &c, const SampleOut &o, hipStream_t s)
+{
+    constexpr int NW = search_waves(KT);
+    if (dealt(c) && c.sampler != HP_SAMPLER_MS) {
+        const int64_t blocks = banded_grid(c, CU_BLOCKS);
+        k_search_sample<KT, NW><<<dim3((unsigned)blocks), dim3(WAVE * NW), 0, s>>>(c, o);
+        return;
+    }
+    const int64_t blocks = wave_grid(c);
+    if (blocks == 0) return;
+    const dim3 grid((unsigned)blocks), block(WAVE);
+    if (c.sampler == HP_SAMPLER_MS) k_search_ms<KT><<<grid, block, 0, s>>>(c, o);
+    else k_search_sample<KT, 1><<<grid, block, 0, s>>>(c, o);
 }
 
 hipError_t launch_search_sample(const SearchCtx &ctx, const SampleOut &o, int kt, hipStream_t s)
 {
     SearchCtx c = ctx;
-    if (c.chunk <= 0) c.chunk = default_chunk(c);
-    const int64_t blocks = banded_grid(c, c.blocks > 0 ? c.blocks : DEFAULT_SEARCH_BLOCKS);
-    if (blocks == 0) return hipSuccess;
-    const dim3 grid((unsigned)blocks), block(WAVE);
-    if (c.sampler == HP_SAMPLER_MS) {
-        switch (kt) {
-        case 4: k_search_ms_k4<<<grid, block, 0, s>>>(c, o); break;
-        case 8: k_search_ms_k8<<<grid, block, 0, s>>>(c, o); break;
-        case 16: k_search_ms_k16<<<grid, block, 0, s>>>(c, o); break;
-        default: k_search_ms_k32<<<grid, block, 0, s>>>(c, o); break;
-        }
-        return hipGetLastError();
-    }
+    if (c.chunk <= 0) c.chunk = default_chunk(c, SEARCH_WALK);
     switch (kt) {
-    case 4: k_search_sample_k4<<<grid, block, 0, s>>>(c, o); break;
-    case 8: k_search_sample_k8<<<grid, block, 0, s>>>(c, o); break;
-    case 16: k_search_sample_k16<<<grid, block, 0, s>>>(c, o); break;
-    default: k_search_sample_k32<<<grid, block, 0, s>>>(c, o); break;
+    case 4: launch_search_k<4>(c, o, s); break;
+    case 8: launch_search_k<8>(c, o, s); break;
+    case 16: launch_search_k<16>(c, o, s); break;
+    default: launch_search_k<32>(c, o, s); break;
     }
     return hipGetLastError();
 }
