@@ -1,8 +1,9 @@
 """The search's launch shapes: launches of many rays, dealt out inside workgroups
 as large as a CU, against one-wave workgroups; the one-call search and render
 with lists of every length, both samplers and decoders, on both sides of its
-chunk rule, against the separate calls.  All equal bit for bit (the same
-operations in the same order)."""
+chunk rule, against the separate calls; K nearest points in windows on both
+sides of the limits between slot runs and buckets, against the oracle.  All
+equal bit for bit (the same operations in the same order)."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +12,7 @@ from paper_2404_14044_amd import hashpoint as hp
 from paper_2404_14044_amd import scenes
 
 from test_gpu_fused import _both
-from test_gpu_search_groups import _scene
+from test_gpu_search_groups import _check_knp, _scene
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +69,12 @@ def test_one_call_is_the_separate_calls(W, H, ms, K, prec):
     p = sc.params.replace(sampler=1, ms_steps=ms) if ms else sc.params
     sc.feat[:] = np.random.default_rng(K).normal(size=sc.feat.shape)
     _both(sc, p, prec)
+
+
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("n", [600, 640, 641, 700, 6300, 6400, 6401, 7000])
+def test_nearest_points_of_crowded_windows(n, layout):
+    """A 5 x 3 view whose rays' windows all hold the whole cloud of n points."""
+    rng = np.random.default_rng(n)
+    xyz = rng.uniform([-0.02, -0.02, 2.2], [0.02, 0.02, 2.9], (n, 3))
+    _check_knp(_scene(xyz, 5, 3, radius=1.2, layout=layout), 12)
