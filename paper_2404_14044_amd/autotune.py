@@ -36,12 +36,12 @@ SPACE = {
     "search_blocks": (0, 8192, 16384, 32768, 65536, 131072),
     "search_band": (800, 1600, 3200, 12800),
     "window_shape": (hp.HP_WINDOW_DISC, hp.HP_WINDOW_SQUARE),
-    "render_rays": (16, 32, 64),
+    "render_rays": (0, 16, 32, 64),
     "render_blocks": (0, 3072, 6144, 12288),
 }
 # the library's defaults (0: by the number of rays), the descent's start
 DEFAULTS = {"layout": hp.HP_LAYOUT_ROWMAJOR, "search_chunk": 0, "search_blocks": 0,
-            "search_band": 1600, "window_shape": hp.HP_WINDOW_DISC, "render_rays": 16,
+            "search_band": 1600, "window_shape": hp.HP_WINDOW_DISC, "render_rays": 0,
             "render_blocks": 0}
 
 

@@ -1,6 +1,6 @@
 // Decode and composite the samples (Sec. 3.4, Eq. 2).
 //
-// One wave per chunk of RPW consecutive rays (16 by default): eight waves
+// One wave per chunk of RPW consecutive rays: eight waves
 // per workgroup, one chunk each, with the decoder weights packed once per
 // workgroup into the LDS (k_render_shared); the persistent grid and chunks
 // too large for that: one wave per workgroup with the weights in its
@@ -304,14 +304,22 @@ static void launch_render_rpw(const RenderArgs &a, int precision, int64_t blocks
     }
 }
 
+// Rays per chunk where the caller names none: 16, whose samples fill tiles best,
+// or 4 up to FEW_RAYS rays, which keep all CUs busy for less time (frames, us, 16
+// / 4 rays per chunk: FP32 64x64 100 / 84, 128x128 96 / 85; BF16 200x200 465 / 445,
+// 300x300 360 / 346; from there on the emptier tiles cost more: 400x400 FP32
+// 211 / 223).
+constexpr int64_t FEW_RAYS = 98304;
+
 hipError_t launch_render(const RenderArgs &a, int precision, hipStream_t s)
 {
-    const int rpw = a.rpw == 32 || a.rpw == 64 ? a.rpw : 16;
+    const int rpw = a.rpw > 0 ? a.rpw : a.blocks == 0 && a.n_rays <= FEW_RAYS ? 4 : 16;
     const int64_t chunks = (a.n_rays + rpw - 1) / rpw;
     if (chunks == 0) return hipSuccess;
     const bool persist = a.blocks > 0 && a.blocks < chunks;
     const int64_t blocks = persist ? a.blocks : chunks;
-    if (rpw == 16) launch_render_rpw<16>(a, precision, blocks, persist, s);
+    if (rpw == 4) launch_render_rpw<4>(a, precision, blocks, persist, s);
+    else if (rpw == 16) launch_render_rpw<16>(a, precision, blocks, persist, s);
     else if (rpw == 64) launch_render_rpw<64>(a, precision, blocks, persist, s);
     else launch_render_rpw<32>(a, precision, blocks, persist, s);
     return hipGetLastError();
