@@ -10,7 +10,7 @@
 //   k_scan_*       counts         -> exclusive offsets, three passes
 //   k_scatter      (view, point)  -> 64-bit key (z bits, point index) per slot
 //   k_sort_small   one lane per bucket of at most 16 points, register network
-//   k_sort_listed  one wave per bucket of 17..128 points, register bitonic;
+//   k_sort_listed  16 lanes per bucket of 17..128 points, register bitonic;
 //                  one workgroup per larger bucket, bitonic in LDS or global
 //   k_materialize  one lane per slot: camera-space point and index (from pcam)
 #include "hp_device.hpp"
@@ -281,9 +281,9 @@ struct SlotOut {
     int32_t *perm;
 };
 
-__device__ __forceinline__ const float4 *bucket_pcam(const SlotOut &o, int b)
+// (vi: a view at or before bucket b's)
+__device__ __forceinline__ const float4 *bucket_pcam(const SlotOut &o, int b, int vi = 0)
 {
-    int vi = 0;
     while (vi + 1 < o.n_views && o.views[vi + 1].bucket_base <= b) ++vi;
     return o.pcam + (int64_t)vi * o.n;
 }
@@ -543,7 +543,13 @@ __global__ void __launch_bounds__(SB_T) k_scatter_sb(const int2 *__restrict__ kz
 // any cell beyond those (a row-major grid wider than about 2,000 buckets, or
 // a superbucket that reaches far into a second view).  Depths of binned
 // points are positive and finite, so their bits order as the values do.
-constexpr int FIN_T = 512;  // threads of a superbucket's workgroup
+//
+// FIN_T: threads of a superbucket's workgroup.  With three workgroups of 512 a
+// CU the object view's superbuckets take one round; a table of few superbuckets
+// (FIN_FEW) leaves most CUs idle anyway and its workgroups wait for one chain of
+// loads after another, so those are twice as wide (64x64 view of 20k points:
+// 36 to 33 us; object at 64x64, whole frame 1486 to 1350).
+constexpr int FIN_FEW = 256;
 constexpr int FIN_CELLS = 512;
 
 // depth cell of bucket b of a view (bucket_base, Wg, cell_base, ncx)
@@ -555,15 +561,12 @@ __device__ __forceinline__ int cell_of_bucket(int layout, int b, int base, int w
     return cbase + (by >> CELL_SHIFT) * ncx + (bx >> CELL_SHIFT);
 }
 
-__global__ void __launch_bounds__(FIN_T) __attribute__((amdgpu_waves_per_eu(6, 8))) k_finalize_sb(const int4 *__restrict__ rec,
-                                                      const int32_t *__restrict__ sb_off,
-                                                      int64_t n_buckets,
-                                                      int32_t *__restrict__ offsets,
-                                                      uint64_t *__restrict__ skey,
-                                                      int32_t *__restrict__ big_list,
-                                                      int32_t *__restrict__ big_n,
-                                                      float *__restrict__ bucket_z, SlotOut so,
-                                                      int layout, uint32_t *__restrict__ cell_zmin)
+template <int FIN_T>
+__global__ void __launch_bounds__(FIN_T) __attribute__((amdgpu_waves_per_eu(FIN_T == 512 ? 6 : 4, 8)))
+k_finalize_sb(const int4 *__restrict__ rec, const int32_t *__restrict__ sb_off, int64_t n_buckets,
+              int32_t *__restrict__ offsets, uint64_t *__restrict__ skey, int32_t *__restrict__ big_list,
+              int32_t *__restrict__ big_n, float *__restrict__ bucket_z, SlotOut so, int layout,
+              uint32_t *__restrict__ cell_zmin)
 {
     __shared__ int cnt[SB];
     __shared__ int cur[SB];
@@ -575,8 +578,12 @@ __global__ void __launch_bounds__(FIN_T) __attribute__((amdgpu_waves_per_eu(6, 8
     const int r0 = sb_off[sb], r1 = sb_off[sb + 1];
     // the view of the superbucket's first bucket, and the first cell of that
     // bucket's cell row (row-major) or its cell (tiles)
+    // (views looked at 64 at a time: one by one each load would wait for the one before)
     int v0 = 0;
-    while (v0 + 1 < so.n_views && so.views[v0 + 1].bucket_base <= key0) ++v0;
+    for (int at = 1; at < so.n_views; at += WAVE) {
+        const int v = min(at + lane_id(), so.n_views - 1);
+        v0 += popc64(ballot(so.views[v].bucket_base <= key0) & ballot(at + lane_id() < so.n_views));
+    }
     const int base0 = so.views[v0].bucket_base, wg0 = so.views[v0].Wg;
     const int cbase0 = so.views[v0].cell_base, ncx0 = so.views[v0].ncx;
     const int end0 = base0 + wg0 * so.views[v0].Hg;
@@ -663,11 +670,8 @@ __global__ void __launch_bounds__(FIN_T) __attribute__((amdgpu_waves_per_eu(6, 8
         uint64_t first = ~0ull;
         if (n_b > 0) {
             // sorted slots become table points right away
-            const float4 *pc = bucket_pcam(so, b);
-            if (n_b == 1) {
-                first = skey[start];
-                put_slot(so, pc, start, first);
-            } else if (n_b <= 4) {
+            const float4 *pc = bucket_pcam(so, b, v0);
+            if (n_b <= 4) {
                 first = sort_bucket_to_slots<4>(skey, start, n_b, so, pc);
             } else if (n_b <= 8) {
                 first = sort_bucket_to_slots<8>(skey, start, n_b, so, pc);
@@ -717,9 +721,50 @@ __device__ void block_flip_bitonic(int cnt, Load ld, Store st)
     }
 }
 
-// Buckets of 17..128 points: one wave each, a register bitonic sort across
-// the wave (one or two keys per lane), no LDS and no workgroup barrier.
+// Buckets of 17..128 points: a row of 16 lanes each, four at a time per wave,
+// sorted in the row's registers (two, four or eight keys per lane by the largest
+// of the four); no LDS and no workgroup barrier.  Bound by the sorting network's
+// vector instructions when a wave sorted one bucket at a time, most of them of
+// fewer than 32 points, over 64 lanes (16 views of 1M points: 401 to 269 us).
 // (workgroup `blk` of `nblk` taking this role)
+template <int R>
+__device__ __forceinline__ void sort_row(uint64_t *__restrict__ skey, int start, int cnt, bool first,
+                                         const float4 *pc, const SlotOut &so, float *bz)
+{
+    const int k16 = lane_id() & 15;
+    uint64_t x[R];
+#pragma unroll
+    for (int e = 0; e < R; ++e) x[e] = 16 * e + k16 < cnt ? skey[start + 16 * e + k16] : KEY_NONE;
+    row_sort(x);
+    if (!first) return;
+    if (k16 == 0) *bz = __uint_as_float((uint32_t)(x[0] >> 32));
+    if (so.pts) {
+        // (gathered before they are stored, up to four at a time; see sort_bucket_to_slots)
+        typedef float fx4 __attribute__((ext_vector_type(4)));
+        const fx4 *src = reinterpret_cast<const fx4 *>(pc);
+        fx4 *dst = reinterpret_cast<fx4 *>(so.pts);
+        constexpr int G = R < 4 ? R : 4;
+#pragma unroll
+        for (int e0 = 0; e0 < R; e0 += G) {
+            fx4 v[G];
+#pragma unroll
+            for (int e = 0; e < G; ++e)
+                if (R * k16 + e0 + e < cnt) v[e] = src[(int32_t)(uint32_t)x[e0 + e]];
+#pragma unroll
+            for (int e = 0; e < G; ++e) {
+                if (R * k16 + e0 + e < cnt) {
+                    dst[start + R * k16 + e0 + e] = v[e];
+                    so.perm[start + R * k16 + e0 + e] = (int32_t)(uint32_t)x[e0 + e];
+                }
+            }
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < R; ++e)
+            if (R * k16 + e < cnt) skey[start + R * k16 + e] = x[e];
+    }
+}
+
 __device__ __forceinline__ void sort_mid(const int32_t *__restrict__ offsets,
                                          uint64_t *__restrict__ skey,
                                          const int32_t *__restrict__ big_list,
@@ -728,34 +773,26 @@ __device__ __forceinline__ void sort_mid(const int32_t *__restrict__ offsets,
                                          int nblk)
 {
     const int nbig = big_n[0];
-    const int l = lane_id();
+    const int row = lane_id() >> 4;
     const int waves = blockDim.x / WAVE;
-    for (int it = blk * waves + (threadIdx.x >> 6); it < nbig; it += nblk * waves) {
-        const int b = big_list[it];
+    for (int it = 4 * (blk * waves + (threadIdx.x >> 6)); it < nbig; it += 4 * nblk * waves) {
+        const bool live = it + row < nbig;  // (rows past the list repeat its last bucket, unused)
+        const int b = big_list[live ? it + row : nbig - 1];
         const int start = offsets[b];
         const int cnt = offsets[b + 1] - start;
-        uint64_t x = l < cnt ? skey[start + l] : ~0ull;
-        if (cnt <= WAVE) {
-            x = wave_sort_fast(x);
-        } else {
-            // 128 keys: an ascending and a descending run, the lane-wise
-            // half-cleaner, then both halves sorted
-            uint64_t y = WAVE + l < cnt ? skey[start + WAVE + l] : ~0ull;
-            x = wave_sort_fast(x);
-            y = wave_sort_desc(y);
-            const uint64_t lo = umin64(x, y), hi = umax64(x, y);
-            x = wave_merge_low_fast(lo, ~0ull);
-            y = wave_merge_low_fast(hi, ~0ull);
-            if (WAVE + l < cnt) {
-                if (so.pts) put_slot(so, bucket_pcam(so, b), start + WAVE + l, y);
-                else skey[start + WAVE + l] = y;
+        const float4 *pc = nullptr;
+        if (so.pts) {
+            int vi = 0;
+            for (int at = 1; at < so.n_views; at += 16) {
+                const int v = at + (lane_id() & 15);
+                const uint64_t m = ballot(v < so.n_views && so.views[min(v, so.n_views - 1)].bucket_base <= b);
+                vi += __builtin_popcount((uint32_t)(m >> (16 * row)) & 0xffffu);
             }
+            pc = so.pcam + (int64_t)vi * so.n;
         }
-        if (l < cnt) {
-            if (so.pts) put_slot(so, bucket_pcam(so, b), start + l, x);
-            else skey[start + l] = x;
-        }
-        if (l == 0) bucket_z[b] = __uint_as_float((uint32_t)(x >> 32));
+        if (ballot(cnt > 64)) sort_row<8>(skey, start, cnt, live, pc, so, bucket_z + b);
+        else if (ballot(cnt > 32)) sort_row<4>(skey, start, cnt, live, pc, so, bucket_z + b);
+        else sort_row<2>(skey, start, cnt, live, pc, so, bucket_z + b);
     }
 }
 
@@ -794,7 +831,7 @@ __device__ __forceinline__ void sort_big(const int32_t *__restrict__ offsets,
 }
 
 // The listed buckets in one launch: the first MID_BLOCKS workgroups sort those
-// of 17..128 points (a wave each), the other BIG_BLOCKS the larger ones.
+// of 17..128 points (16 lanes each), the other BIG_BLOCKS the larger ones.
 constexpr int MID_BLOCKS = 1024;
 constexpr int BIG_BLOCKS = 256;
 static_assert(BIG_T == 256, "both roles run 256-thread workgroups");
@@ -906,9 +943,13 @@ hipError_t launch_build(const float *xyz, int64_t n, const ViewSet &vs, int64_t 
         // (the records sit in pts: a superbucket's workgroup overwrites only
         // its own range, after reading all of it)
         const SlotOut so{tw.pcam, n, tw.views, V, tw.pts, tw.perm};
-        k_finalize_sb<<<(unsigned)nsb, FIN_T, 0, s>>>(reinterpret_cast<const int4 *>(tw.pts), tw.sb_off,
-                                                     n_buckets, tw.offsets, tw.skey, tw.big_list,
-                                                     tw.big_n, tw.bucket_z, so, vs.layout, tw.cell_zmin);
+        const auto finalize = [&](auto kernel, int threads) {
+            kernel<<<(unsigned)nsb, threads, 0, s>>>(reinterpret_cast<const int4 *>(tw.pts), tw.sb_off, n_buckets,
+                                                     tw.offsets, tw.skey, tw.big_list, tw.big_n, tw.bucket_z, so,
+                                                     vs.layout, tw.cell_zmin);
+        };
+        if (nsb <= FIN_FEW) finalize(k_finalize_sb<1024>, 1024);
+        else finalize(k_finalize_sb<512>, 512);
         k_sort_listed<<<MID_BLOCKS + BIG_BLOCKS, 256, 0, s>>>(tw.offsets, tw.skey, tw.big_list, tw.big_n,
                                                             tw.bucket_z, n_buckets, so);
         return hipGetLastError();
