@@ -52,6 +52,7 @@ MLP_FLOP_PER_SAMPLE = 2 * (32 * 64 + 64 * 64 + 64 * 4)   # 12,800
 CHIP_CUS, CHIP_GHZ = 256, 2.4
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "forward_path_objects_1m.md")
+SEARCH_KERNEL = "k_search_sample<8,16>"  # the default search launch of the main step (lists of up to 8)
 RENDER_KERNEL = "k_render_shared<1,16>"  # the default BF16 render launch (HP_BF16 = 1)
 COUNTER_SOURCES = ("paper_2404_14044_amd/csrc", "include")
 
@@ -236,7 +237,7 @@ def main():
     }
     counters = load_counters()
     if counters is not None:
-        ks = counters["kernels"].get("k_search_sample_k8")
+        ks = counters["kernels"].get(SEARCH_KERNEL)
         if ks:
             traffic = (ks["FETCH_SIZE_kib"] * counters["fetch_scale"]
                        + ks["WRITE_SIZE_kib"] * counters["write_scale"]) * 1024.0
