@@ -11,7 +11,8 @@
 //   k_scatter      (view, point)  -> 64-bit key (z bits, point index) per slot
 //   k_sort_small   one lane per bucket of at most 16 points, register network
 //   k_sort_listed  16 lanes per bucket of 17..128 points, register bitonic;
-//                  one workgroup per larger bucket, bitonic in LDS or global
+//                  a wave per bucket of up to 512, one workgroup per larger one,
+//                  bitonic in LDS or global
 //   k_materialize  one lane per slot: camera-space point and index (from pcam)
 #include "hp_device.hpp"
 #include "hp_kernels.hpp"
@@ -721,23 +722,20 @@ __device__ void block_flip_bitonic(int cnt, Load ld, Store st)
     }
 }
 
-// Buckets of 17..128 points: a row of 16 lanes each, four at a time per wave,
-// sorted in the row's registers (two, four or eight keys per lane by the largest
-// of the four); no LDS and no workgroup barrier.  Bound by the sorting network's
-// vector instructions when a wave sorted one bucket at a time, most of them of
-// fewer than 32 points, over 64 lanes (16 views of 1M points: 401 to 269 us).
-// (workgroup `blk` of `nblk` taking this role)
-template <int R>
-__device__ __forceinline__ void sort_row(uint64_t *__restrict__ skey, int start, int cnt, bool first,
+// One bucket's keys sorted in the registers of LANES lanes (16: a row, 64: the
+// wave), R per lane, and written as table points (or keys).
+template <int R, int LANES>
+__device__ __forceinline__ void sort_run(uint64_t *__restrict__ skey, int start, int cnt, bool live,
                                          const float4 *pc, const SlotOut &so, float *bz)
 {
-    const int k16 = lane_id() & 15;
+    const int k = lane_id() & (LANES - 1);
     uint64_t x[R];
 #pragma unroll
-    for (int e = 0; e < R; ++e) x[e] = 16 * e + k16 < cnt ? skey[start + 16 * e + k16] : KEY_NONE;
-    row_sort(x);
-    if (!first) return;
-    if (k16 == 0) *bz = __uint_as_float((uint32_t)(x[0] >> 32));
+    for (int e = 0; e < R; ++e) x[e] = LANES * e + k < cnt ? skey[start + LANES * e + k] : KEY_NONE;
+    if constexpr (LANES == 16) row_sort(x);
+    else wave_sort_many(x);
+    if (!live) return;
+    if (k == 0) *bz = __uint_as_float((uint32_t)(x[0] >> 32));
     if (so.pts) {
         // (gathered before they are stored, up to four at a time; see sort_bucket_to_slots)
         typedef float fx4 __attribute__((ext_vector_type(4)));
@@ -749,22 +747,28 @@ __device__ __forceinline__ void sort_row(uint64_t *__restrict__ skey, int start,
             fx4 v[G];
 #pragma unroll
             for (int e = 0; e < G; ++e)
-                if (R * k16 + e0 + e < cnt) v[e] = src[(int32_t)(uint32_t)x[e0 + e]];
+                if (R * k + e0 + e < cnt) v[e] = src[(int32_t)(uint32_t)x[e0 + e]];
 #pragma unroll
             for (int e = 0; e < G; ++e) {
-                if (R * k16 + e0 + e < cnt) {
-                    dst[start + R * k16 + e0 + e] = v[e];
-                    so.perm[start + R * k16 + e0 + e] = (int32_t)(uint32_t)x[e0 + e];
+                if (R * k + e0 + e < cnt) {
+                    dst[start + R * k + e0 + e] = v[e];
+                    so.perm[start + R * k + e0 + e] = (int32_t)(uint32_t)x[e0 + e];
                 }
             }
         }
     } else {
 #pragma unroll
         for (int e = 0; e < R; ++e)
-            if (R * k16 + e < cnt) skey[start + R * k16 + e] = x[e];
+            if (R * k + e < cnt) skey[start + R * k + e] = x[e];
     }
 }
 
+// Buckets of 17..128 points: a row of 16 lanes each, four at a time per wave,
+// sorted in the row's registers (two, four or eight keys per lane by the largest
+// of the four); no LDS and no workgroup barrier.  Bound by the sorting network's
+// vector instructions when a wave sorted one bucket at a time, most of them of
+// fewer than 32 points, over 64 lanes (16 views of 1M points: 401 to 269 us).
+// (workgroup `blk` of `nblk` taking this role)
 __device__ __forceinline__ void sort_mid(const int32_t *__restrict__ offsets,
                                          uint64_t *__restrict__ skey,
                                          const int32_t *__restrict__ big_list,
@@ -790,13 +794,36 @@ __device__ __forceinline__ void sort_mid(const int32_t *__restrict__ offsets,
             }
             pc = so.pcam + (int64_t)vi * so.n;
         }
-        if (ballot(cnt > 64)) sort_row<8>(skey, start, cnt, live, pc, so, bucket_z + b);
-        else if (ballot(cnt > 32)) sort_row<4>(skey, start, cnt, live, pc, so, bucket_z + b);
-        else sort_row<2>(skey, start, cnt, live, pc, so, bucket_z + b);
+        if (ballot(cnt > 64)) sort_run<8, 16>(skey, start, cnt, live, pc, so, bucket_z + b);
+        else if (ballot(cnt > 32)) sort_run<4, 16>(skey, start, cnt, live, pc, so, bucket_z + b);
+        else sort_run<2, 16>(skey, start, cnt, live, pc, so, bucket_z + b);
     }
 }
 
-// Buckets of more than 128 points: one workgroup each, bitonic in LDS (in
+// Buckets of 129..WAVE_MAX points: one wave each, in its registers (a
+// workgroup's bitonic in LDS waited for a barrier at each of 36 to 45 stages;
+// frame of 1M points at 200x200 446 to 316 us).
+constexpr int WAVE_MAX = 512;
+
+__device__ __forceinline__ void sort_wave(const int32_t *__restrict__ offsets, uint64_t *__restrict__ skey,
+                                          const int32_t *__restrict__ big_list, const int32_t *__restrict__ big_n,
+                                          float *__restrict__ bucket_z, int64_t cap, const SlotOut &so, int blk,
+                                          int nblk)
+{
+    const int nbig = big_n[1];
+    const int waves = blockDim.x / WAVE;
+    for (int it = blk * waves + (threadIdx.x >> 6); it < nbig; it += nblk * waves) {
+        const int b = uniform_i32(big_list[cap - 1 - it]);
+        const int start = offsets[b];
+        const int cnt = offsets[b + 1] - start;
+        if (cnt > WAVE_MAX) continue;
+        const float4 *pc = so.pts ? bucket_pcam(so, b) : nullptr;
+        if (cnt > 256) sort_run<8, WAVE>(skey, start, cnt, true, pc, so, bucket_z + b);
+        else sort_run<4, WAVE>(skey, start, cnt, true, pc, so, bucket_z + b);
+    }
+}
+
+// Buckets of more than WAVE_MAX points: one workgroup each, bitonic in LDS (in
 // global memory beyond BIG_LDS entries).
 __device__ __forceinline__ void sort_big(const int32_t *__restrict__ offsets,
                                          uint64_t *__restrict__ skey,
@@ -805,33 +832,47 @@ __device__ __forceinline__ void sort_big(const int32_t *__restrict__ offsets,
                                          float *__restrict__ bucket_z, int64_t cap, const SlotOut &so,
                                          uint64_t *sh, int blk, int nblk)
 {
+    // (the workgroup's entries, looked at 256 at a time for those above WAVE_MAX)
+    __shared__ int mine[BIG_T], n_mine;
     const int nbig = big_n[1];
-    for (int it = blk; it < nbig; it += nblk) {
-        const int b = big_list[cap - 1 - it];
-        const int start = offsets[b];
-        const int cnt = offsets[b + 1] - start;
-        uint64_t *g = skey + start;
-        if (cnt <= BIG_LDS) {
-            for (int i = threadIdx.x; i < cnt; i += blockDim.x) sh[i] = g[i];
-            __syncthreads();
-            block_flip_bitonic(cnt, [&](int i) { return sh[i]; }, [&](int i, uint64_t v) { sh[i] = v; });
-            for (int i = threadIdx.x; i < cnt; i += blockDim.x) g[i] = sh[i];
-        } else {
-            block_flip_bitonic(cnt, [&](int i) { return g[i]; },
-                               [&](int i, uint64_t v) { g[i] = v; });
+    for (int64_t it0 = blk; it0 < nbig; it0 += (int64_t)nblk * BIG_T) {
+        const int64_t it = it0 + (int64_t)nblk * threadIdx.x;
+        if (threadIdx.x == 0) n_mine = 0;
+        __syncthreads();
+        if (it < nbig) {
+            const int b = big_list[cap - 1 - it];
+            if (offsets[b + 1] - offsets[b] > WAVE_MAX) mine[atomicAdd(&n_mine, 1)] = b;
         }
         __syncthreads();
-        if (so.pts) {
-            const float4 *pc = bucket_pcam(so, b);
-            for (int i = threadIdx.x; i < cnt; i += blockDim.x) put_slot(so, pc, start + i, g[i]);
+        const int n = n_mine;
+        for (int k = 0; k < n; ++k) {
+            const int b = mine[k];
+            const int start = offsets[b];
+            const int cnt = offsets[b + 1] - start;
+            uint64_t *g = skey + start;
+            if (cnt <= BIG_LDS) {
+                for (int i = threadIdx.x; i < cnt; i += blockDim.x) sh[i] = g[i];
+                __syncthreads();
+                block_flip_bitonic(cnt, [&](int i) { return sh[i]; }, [&](int i, uint64_t v) { sh[i] = v; });
+                for (int i = threadIdx.x; i < cnt; i += blockDim.x) g[i] = sh[i];
+            } else {
+                block_flip_bitonic(cnt, [&](int i) { return g[i]; },
+                                   [&](int i, uint64_t v) { g[i] = v; });
+            }
+            __syncthreads();
+            if (so.pts) {
+                const float4 *pc = bucket_pcam(so, b);
+                for (int i = threadIdx.x; i < cnt; i += blockDim.x) put_slot(so, pc, start + i, g[i]);
+            }
+            if (threadIdx.x == 0) bucket_z[b] = __uint_as_float((uint32_t)(g[0] >> 32));
+            __syncthreads();
         }
-        if (threadIdx.x == 0) bucket_z[b] = __uint_as_float((uint32_t)(g[0] >> 32));
         __syncthreads();
     }
 }
 
 // The listed buckets in one launch: the first MID_BLOCKS workgroups sort those
-// of 17..128 points (16 lanes each), the other BIG_BLOCKS the larger ones.
+// of 17..WAVE_MAX points (16 or 64 lanes each), the other BIG_BLOCKS the larger ones.
 constexpr int MID_BLOCKS = 1024;
 constexpr int BIG_BLOCKS = 256;
 static_assert(BIG_T == 256, "both roles run 256-thread workgroups");
@@ -844,9 +885,10 @@ __global__ void __launch_bounds__(256) k_sort_listed(const int32_t *__restrict__
                                                      SlotOut so)
 {
     __shared__ uint64_t sh[BIG_LDS];
-    if (blockIdx.x < MID_BLOCKS)
+    if (blockIdx.x < MID_BLOCKS) {
+        sort_wave(offsets, skey, big_list, big_n, bucket_z, cap, so, blockIdx.x, MID_BLOCKS);
         sort_mid(offsets, skey, big_list, big_n, bucket_z, so, blockIdx.x, MID_BLOCKS);
-    else
+    } else
         sort_big(offsets, skey, big_list, big_n, bucket_z, cap, so, sh, blockIdx.x - MID_BLOCKS,
                  BIG_BLOCKS);
 }

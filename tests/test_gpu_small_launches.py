@@ -33,17 +33,29 @@ def test_four_ray_chunks(W, H, K, S, prec):
 SIZES = [0, 1, 2, 4, 5, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 200]
 
 
+LARGE = [128, 129, 255, 256, 257, 300, 511, 512, 513, 600, 4095, 4096, 4097, 17, 40, 3, 0]
+
+
+@pytest.mark.parametrize("W,H,views", [(21, 9, 1), (21, 9, 17), (800, 700, 2)])
+def test_large_bucket_sizes(W, H, views):
+    _check_sizes(LARGE, W, H, views)
+
+
 @pytest.mark.parametrize("views", [1, 17, 20])
 @pytest.mark.parametrize("W,H", [(21, 9), (800, 700)])
 def test_bucket_sizes(W, H, views):
-    """Row 4 of the view has SIZES points in its first pixels, shuffled so that
-    each wave's four buckets differ, a third of them at equal depths."""
     if views > 1 and W > 100:
         views = 2
+    _check_sizes(SIZES, W, H, views)
+
+
+def _check_sizes(sizes, W, H, views):
+    """Row 4 of the view has `sizes` points in its first pixels, shuffled so that
+    each wave's four buckets differ, a third of them at equal depths."""
     rng = np.random.default_rng(views)
     cam = scenes.pinhole(W, H, 40.0, np.eye(3), np.zeros(3))
     pts = []
-    for u, n in enumerate(rng.permutation(SIZES)):
+    for u, n in enumerate(rng.permutation(sizes)):
         z = rng.uniform(2.0, 3.0, n)
         z[: n // 3] = 2.5
         x = (u + 0.5 + rng.uniform(-0.3, 0.3, n) - cam.cx) / cam.fx * z
