@@ -345,12 +345,10 @@ __device__ __forceinline__ uint64_t flip_keys(uint64_t x)
 // of K lanes, the blocks that must descend hold inverted keys, so that every
 // stage is the same ascending compare-exchange; the keys are re-inverted
 // between block sizes as the block directions change.
-template <bool DESC>
-__device__ __forceinline__ uint64_t wave_sort_dir(uint64_t x)
+__device__ __forceinline__ uint64_t wave_sort_fast(uint64_t x)
 {
     const int l = lane_id();
     x = flip_keys<1, -1>(x);  // K = 2 blocks descend where lane bit 1 is set
-    if constexpr (DESC) x = ~x;
     x = cx_merge<1>(x, l);
     x = flip_keys<1, 2>(x);
     x = cx_merge<2>(x, l);
@@ -360,21 +358,9 @@ __device__ __forceinline__ uint64_t wave_sort_dir(uint64_t x)
     x = cx_merge<8>(x, l);
     x = flip_keys<4, 5>(x);
     x = cx_merge<16>(x, l);
-    x = flip_keys<5, -1>(x);  // one block of 64: ascends (descends with DESC)
+    x = flip_keys<5, -1>(x);  // one block of 64: ascends
     x = cx_merge<32>(x, l);
-    if constexpr (DESC) x = ~x;
     return x;
-}
-
-__device__ __forceinline__ uint64_t wave_sort_fast(uint64_t x) { return wave_sort_dir<false>(x); }
-__device__ __forceinline__ uint64_t wave_sort_desc(uint64_t x) { return wave_sort_dir<true>(x); }
-
-// Keep the 64 smallest of an ascending and a descending wave-sorted list,
-// ascending: their lane-wise minimum is bitonic and holds the 64 smallest;
-// half-cleaners then sort it.
-__device__ __forceinline__ uint64_t wave_merge_low_fast(uint64_t asc, uint64_t desc)
-{
-    return cx_merge<WAVE / 2>(umin64(asc, desc), lane_id());
 }
 
 // Lane p of each quad's value, on all four lanes (p a constant after unrolling).
@@ -1713,17 +1699,6 @@ __device__ __forceinline__ void walk_batch(Lds &sh, int ns, Lists lists, Emit em
     }
     if (live && k16 == 0) ends(ray, sel);
     lds_sync();
-}
-
-__device__ __forceinline__ int wave_min_i32(int v)
-{
-    v = min(v, (int)xor_lane_u32<1>((uint32_t)v));
-    v = min(v, (int)xor_lane_u32<2>((uint32_t)v));
-    v = min(v, (int)xor_lane_u32<4>((uint32_t)v));
-    v = min(v, (int)xor_lane_u32<8>((uint32_t)v));
-    v = min(v, (int)xor_lane_u32<16>((uint32_t)v));
-    v = min(v, (int)xor_lane_u32<32>((uint32_t)v));
-    return v;
 }
 
 // A ray's neighbours in depth order, 64 at a time.  Where the search held all

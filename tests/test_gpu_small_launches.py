@@ -33,6 +33,11 @@ def test_four_ray_chunks(W, H, K, S, prec):
 SIZES = [0, 1, 2, 4, 5, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 200]
 
 
+@pytest.mark.parametrize("views", [1, 2])
+def test_buckets_of_several_blocks(views):
+    _check_sizes([8191, 8192, 8193, 13000, 1025, 1, 0], 21, 9, views)
+
+
 LARGE = [128, 129, 255, 256, 257, 300, 511, 512, 513, 600, 4095, 4096, 4097, 17, 40, 3, 0]
 
 
