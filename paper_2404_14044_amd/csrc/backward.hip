@@ -655,7 +655,29 @@ __global__ void __launch_bounds__(WAVE *BWD_WAVES) k_render_backward(BwdArgs A)
                 for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) df[cb][e] = FT[(4 * q + e) * FROW + 16 * cb + r16];
-                for (int j0 = 0; j0 < nu; j0 += 16) {
+                // M holds zeros where a sample does not name a neighbour, and
+                // zero times an infinity or a NaN is a NaN, which would reach
+                // every point of the tile: a tile with a gradient that is not
+                // finite adds its pairs one by one instead of contracting them.
+                // (their sum is not finite then; a sum that overflows only
+                // takes the slower way.  The test is not measurable: 160k
+                // rays, K = 12, S = 24, FP32 660 us with and without it)
+                float sum = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum += df[0][e] + df[1][e];
+                const bool pairs = ballot(!(__builtin_fabsf(sum) < __builtin_inff())) != 0;
+                if (pairs) {
+                    wave_lds_sync();
+#pragma unroll
+                    for (int m = 0; m < PF; ++m) {
+                        if (rank[m] < 0) continue;
+                        const float *const g = FT + (((uint32_t)key[m] >> 5) & 15u) * FROW;
+                        float *const at = A.grad_feat + (int64_t)tp.index[rank[m]] * HP_FEAT_DIM;
+#pragma unroll 1
+                        for (int c = 0; c < HP_FEAT_DIM; ++c) atomicAdd(at + c, wp[m] * g[c]);
+                    }
+                }
+                for (int j0 = 0; j0 < nu && !pairs; j0 += 16) {
                     *reinterpret_cast<float4 *>(&tp.m[r16][4 * q]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                     wave_lds_sync();
 #pragma unroll
