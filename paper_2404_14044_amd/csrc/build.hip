@@ -866,11 +866,18 @@ __device__ __forceinline__ void sort_block(const uint64_t *g, int cnt, uint64_t 
 }
 
 // Buckets of more than WAVE_MAX points: one workgroup each, up to BIG_LDS keys
-// in LDS.  Beyond, blocks of BIG_LDS keys are sorted in place and a key's final
-// rank found among the blocks in the same way; a table kept as keys (no points
-// to write to) is sorted by a bitonic network in global memory instead.
+// in LDS.  Up to RANK_MAX, blocks of BIG_LDS keys are sorted in place and a key's
+// final rank found among the blocks in the same way; beyond, and for a table kept
+// as keys (no points to write to), a bitonic network in global memory.
 // (Bitonic at every size, with a barrier at each stage: frame of 1M points at 100x100
 // 828 us against 611, at 36x36 2,320 against 1,636.)
+// RANK_MAX: each key is looked up in every other block, so the ranks take a time
+// that grows with the square of the bucket, the network one that grows with n
+// log^2 n.  (Builds, us, ranks / network: one bucket of 8,192 points 295 / 460, 16,384
+// 702 / 970, 24,576 1325 / 1804, 32,768 2130 / 2148, 65,536 7192 / 4687; 60 buckets of
+// 24,576 points 3455 / 3512, of 32,768 5224 / 4424, of 65,536 15480 / 10475.)
+constexpr int RANK_MAX = 6 * BIG_LDS;
+
 __device__ __forceinline__ void sort_big(const int32_t *__restrict__ offsets,
                                          uint64_t *skey,
                                          const int32_t *__restrict__ big_list,
@@ -904,7 +911,7 @@ __device__ __forceinline__ void sort_big(const int32_t *__restrict__ offsets,
             };
             if (cnt <= BIG_LDS) {
                 sort_block(g, cnt, sh, place);
-            } else if (so.pts) {
+            } else if (so.pts && cnt <= RANK_MAX) {
                 for (int o = 0; o < cnt; o += BIG_LDS)
                     sort_block(g + o, min(BIG_LDS, cnt - o), sh, [&](int rank, uint64_t key) { g[o + rank] = key; });
                 for (int i = threadIdx.x; i < cnt; i += BIG_T) {
@@ -918,7 +925,11 @@ __device__ __forceinline__ void sort_big(const int32_t *__restrict__ offsets,
             } else {
                 block_flip_bitonic(cnt, [&](int i) { return g[i]; },
                                    [&](int i, uint64_t v) { g[i] = v; });
-                if (threadIdx.x == 0) bucket_z[b] = __uint_as_float((uint32_t)(g[0] >> 32));
+                if (so.pts) {
+                    for (int i = threadIdx.x; i < cnt; i += BIG_T) place(i, g[i]);
+                } else if (threadIdx.x == 0) {
+                    bucket_z[b] = __uint_as_float((uint32_t)(g[0] >> 32));
+                }
             }
             __syncthreads();
         }

@@ -1,0 +1,45 @@
+"""Tables whose buckets hold far more points than a workgroup sorts in its LDS (a
+cloud seen in a few pixels, coincident points): the order on both sides of the
+limit between the two ways to sort them, against the oracle's, and how the time
+grows with the bucket."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2404_14044_amd import hashpoint as hp
+from paper_2404_14044_amd import scenes
+
+from test_gpu_small_launches import _check_sizes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("views", [1, 2])
+def test_order_of_crowded_buckets(views):
+    _check_sizes([24_575, 24_576, 24_577, 131_075, 4096, 3, 0], 21, 9, views)
+
+
+def test_time_of_one_bucket_does_not_grow_with_its_square():
+    """One bucket of 32,768 and of 262,144 points.  A sorting network's work grows
+    by 8 log2(262144)^2 / log2(32768)^2 = 11.5, work that grows with the square of
+    the bucket by 64: the bound is their geometric mean, 27."""
+    cam = scenes.pinhole(21, 9, 40.0, np.eye(3), np.zeros(3))
+    p = scenes.default_params(0.002, 1.0, 5.0, K=4, S=8)
+    times = []
+    for n in (32_768, 262_144):
+        rng = np.random.default_rng(n)
+        z = rng.uniform(2.0, 3.0, n)
+        xy = (np.array([[7.5, 4.5]]) + rng.uniform(-0.3, 0.3, (n, 2)) - [cam.cx, cam.cy]) / cam.fx * z[:, None]
+        xyz = torch.from_numpy(np.concatenate([xy, z[:, None]], 1).astype(np.float32)).cuda()
+        ws = torch.empty(hp.table_workspace(n, [cam], p), dtype=torch.uint8, device="cuda")
+        hp.build_table(xyz, [cam], p, ws=ws)
+        best = float("inf")
+        for _ in range(3):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            hp.build_table(xyz, [cam], p, ws=ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        times.append(best)
+    assert times[1] <= 27 * times[0], times
