@@ -595,6 +595,21 @@ __device__ __forceinline__ RayGeom load_ray(const RayGeom &src)
     return g;
 }
 
+// Rays from ray i of a pass on that are searched together, at most `most`
+// <= GROUP: bit RS_LANES k of `joined` is set where ray k follows ray k - 1.
+__host__ __device__ constexpr int group_size(uint64_t joined, int i, int most)
+{
+    // (the bits from ray i on come down first, so that no shift below reaches
+    // the width of the mask, whichever ray is the pass's last)
+    const uint64_t run = joined >> (RS_LANES * i);
+    int m = 1;
+    while (m < most && ((run >> (RS_LANES * m)) & 1ull)) ++m;
+    return m;
+}
+static_assert(RS_LANES * RS_CAP == WAVE && group_size(~0ull, RS_CAP - 1, GROUP) == 1 &&
+                  group_size(~0ull, 0, GROUP) == GROUP,
+              "groups end with the pass");
+
 // Persistent iteration over the rays of a launch.  Workgroups take chunks of
 // c.chunk consecutive rays (neighbouring pixels share table buckets).  They are
 // dealt to the eight XCDs round-robin (workgroup b runs on XCD b % 8), each with
@@ -694,8 +709,7 @@ __device__ __forceinline__ void for_each_group_banded(RayGeom *rs, int *take, Gr
                                     ballot(u > 0);
             for (uint64_t todo = near; todo != 0;) {
                 const int i = __builtin_ctzll(todo) / RS_LANES;
-                int m = 1;
-                while (m < MAXG && ((joined >> (RS_LANES * (i + m))) & 1ull)) ++m;
+                const int m = group_size(joined, i, MAXG);
                 todo &= ~(((1ull << (RS_LANES * m)) - 1ull) << (RS_LANES * i));
                 groups(m, (int)ray_at(s0 + i), i, todo == 0);
             }
