@@ -1026,7 +1026,7 @@ __device__ __forceinline__ void search_group(const RayGeom *rs, RaySlot *slot, S
             // bounds only (margins of 1e-3 px and 0.1% dwarf 1-ulp approximations)
             const float Dp = D - 0.01f;
             const float zc = ((frL2 * __builtin_amdgcn_rcpf(Dp) + two_rw) * inv_L) * 1.001f + 1e-5f;
-            return (Dp > 0.0f) & (Dp > dinf) & (zc < z_hi) ? zc : z_hi;
+            return ((Dp > 0.0f) & (Dp > dinf) & (zc < z_hi)) ? zc : z_hi;
         };
         // distance of buckets x .. x + nx, y .. y + ny from the nearest of the rays' pixel centres
         auto distance = [&](int x, int y, int nx, int ny) -> float {
