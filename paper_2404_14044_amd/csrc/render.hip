@@ -284,41 +284,50 @@ __global__ void __launch_bounds__(WAVE *SHARED_WAVES) k_render_shared(RenderArgs
 }
 
 template <int RPW>
+static void launch_shared(const RenderArgs &a, int precision, hipStream_t s)
+{
+    const size_t shmem = (size_t)SHARED_WAVES * RPW * a.S * sizeof(float4);
+    const int64_t chunks = (a.n_rays + RPW - 1) / RPW;
+    const dim3 grid((unsigned)((chunks + SHARED_WAVES - 1) / SHARED_WAVES)), block(WAVE * SHARED_WAVES);
+    if (precision == HP_BF16) k_render_shared<HP_BF16, RPW><<<grid, block, shmem, s>>>(a);
+    else k_render_shared<HP_FP32, RPW><<<grid, block, shmem, s>>>(a);
+}
+
+template <int RPW>
 static void launch_render_rpw(const RenderArgs &a, int precision, int64_t blocks, bool persist,
                               hipStream_t s)
 {
     const size_t shmem = (size_t)RPW * a.S * sizeof(float4);
     const dim3 grid((unsigned)blocks), block(WAVE);
-    const int64_t chunks = (a.n_rays + RPW - 1) / RPW;
-    const unsigned g = (unsigned)((chunks + SHARED_WAVES - 1) / SHARED_WAVES);
-    const bool shared = !persist && shmem * SHARED_WAVES <= SHARED_DYN_MAX;
-    const size_t shm = shmem * SHARED_WAVES;
-    if (precision == HP_BF16) {
-        if (shared) k_render_shared<HP_BF16, RPW><<<g, WAVE * SHARED_WAVES, shm, s>>>(a);
-        else if (persist) k_render_bf16<RPW, true><<<grid, block, shmem, s>>>(a);
+    if (!persist && shmem * SHARED_WAVES <= SHARED_DYN_MAX) {
+        launch_shared<RPW>(a, precision, s);
+    } else if (precision == HP_BF16) {
+        if (persist) k_render_bf16<RPW, true><<<grid, block, shmem, s>>>(a);
         else k_render_bf16<RPW, false><<<grid, block, shmem, s>>>(a);
     } else {
-        if (shared) k_render_shared<HP_FP32, RPW><<<g, WAVE * SHARED_WAVES, shm, s>>>(a);
-        else if (persist) k_render_fp32<RPW, true><<<grid, block, shmem, s>>>(a);
+        if (persist) k_render_fp32<RPW, true><<<grid, block, shmem, s>>>(a);
         else k_render_fp32<RPW, false><<<grid, block, shmem, s>>>(a);
     }
 }
 
 // Rays per chunk where the caller names none: 16, whose samples fill tiles best,
-// or 4 up to FEW_RAYS rays, which keep all CUs busy for less time (frames, us, 16
+// or FEW_RPW up to FEW_RAYS rays, which keep all CUs busy for less time (frames, us, 16
 // / 4 rays per chunk: FP32 64x64 100 / 84, 128x128 96 / 85; BF16 200x200 465 / 445,
 // 300x300 360 / 346; from there on the emptier tiles cost more: 400x400 FP32
 // 211 / 223).
 constexpr int64_t FEW_RAYS = 98304;
+constexpr int FEW_RPW = 4;
+static_assert(SHARED_WAVES * FEW_RPW * HP_MAX_SAMPLES * sizeof(float4) <= SHARED_DYN_MAX,
+              "chunks of few rays exceed the shared kernel's LDS");
 
 hipError_t launch_render(const RenderArgs &a, int precision, hipStream_t s)
 {
-    const int rpw = a.rpw > 0 ? a.rpw : a.blocks == 0 && a.n_rays <= FEW_RAYS ? 4 : 16;
+    const int rpw = a.rpw > 0 ? a.rpw : a.blocks == 0 && a.n_rays <= FEW_RAYS ? FEW_RPW : 16;
     const int64_t chunks = (a.n_rays + rpw - 1) / rpw;
     if (chunks == 0) return hipSuccess;
     const bool persist = a.blocks > 0 && a.blocks < chunks;
     const int64_t blocks = persist ? a.blocks : chunks;
-    if (rpw == 4) launch_render_rpw<4>(a, precision, blocks, persist, s);
+    if (rpw == FEW_RPW) launch_shared<FEW_RPW>(a, precision, s);
     else if (rpw == 16) launch_render_rpw<16>(a, precision, blocks, persist, s);
     else if (rpw == 64) launch_render_rpw<64>(a, precision, blocks, persist, s);
     else launch_render_rpw<32>(a, precision, blocks, persist, s);
