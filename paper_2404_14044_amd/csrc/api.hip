@@ -406,7 +406,6 @@ hp_status hp_search_render(const hp_table *tab, const hp_camera *cams, int32_t n
     a.depth = depth;
     a.acc = acc;
     a.n_sel = n_sel;
-    a.K = p->K;
     const hipError_t e =
         hp::launch_fused(c, a, knn_template(p->K), precision, (hipStream_t)stream);
     return e == hipSuccess ? HP_OK : hip_fail(e);

@@ -63,7 +63,7 @@ struct BwdWave {
     float4 o[BWD_CHUNK];            // raw decoder outputs, then their gradients
     float T[BWD_CHUNK];             // transmittance in front of each sample
     float t[BWD_CHUNK];             // ray parameter of each sample
-    int32_t pre[WAVE + 1];          // sample prefix over the rays taken
+    int32_t pre[WAVE];              // sample prefix over the rays taken
     float inv[16];                  // tile: 1 / sum of the inverse-distance weights
     float4 w[16][2];                // tile: eight inverse-distance weights per sample
     float F[HP_FEAT_DIM * TROW];    // tile: aggregated features [feature][sample], later their gradients [sample][feature]
@@ -330,7 +330,6 @@ __global__ void __launch_bounds__(WAVE *BWD_WAVES) k_render_backward(BwdArgs A)
         const int inc = wave_incl_scan_i32(ns);
         sh.pre[l] = inc - ns;
         const int taken_samples = readlane_i32(inc, WAVE - 1);
-        if (l == 0) sh.pre[WAVE] = taken_samples;
         wave_lds_sync();
 
         // as many consecutive rays at a time as BWD_CHUNK samples hold (a

@@ -69,7 +69,6 @@ struct FusedArgs {
     float bg[3];
     float *rgb, *depth, *acc;  // depth, acc nullable
     int32_t *n_sel;            // nullable
-    int32_t K;
 };
 
 int fused_max_samples();
