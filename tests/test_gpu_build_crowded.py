@@ -9,7 +9,7 @@ import torch
 from paper_2404_14044_amd import hashpoint as hp
 from paper_2404_14044_amd import scenes
 
-from test_gpu_small_launches import _check_sizes
+from test_gpu_small_launches import LARGE, SIZES, _check_sizes
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +43,14 @@ def test_time_of_one_bucket_does_not_grow_with_its_square():
             best = min(best, a.elapsed_time(b))
         times.append(best)
     assert times[1] <= 27 * times[0], times
+
+
+@pytest.mark.parametrize("sizes", [SIZES, LARGE, [8191, 8192, 8193, 13_000, 24_577, 1025, 1, 0]],
+                         ids=["small", "large", "blocks"])
+def test_one_level_build(sizes):
+    """A view of more than 2^23 buckets is built in one level, which sorts the
+    buckets' keys and makes the points of them afterwards."""
+    cam = scenes.pinhole(3000, 3000, 40.0, np.eye(3), np.zeros(3))
+    g, _ = hp.view_bounds(cam, scenes.default_params(0.002, 1.0, 5.0, K=4, S=8))
+    assert (3000 + 2 * g) ** 2 > 2 ** 23
+    _check_sizes(sizes, 3000, 3000, 1)
