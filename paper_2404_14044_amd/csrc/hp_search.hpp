@@ -838,8 +838,8 @@ __device__ __forceinline__ float quad_min_f32(float v) { return -quad_max_f32(-v
 //    less than looking at it);
 //  - buckets: elsewhere the buckets of the 8x8-bucket cells that reach into
 //    the window are probed and those that may hold a neighbour listed; they
-//    are taken 64 at a time, one per lane, and every lane walks its bucket's
-//    points from the nearest on.  Buckets are ordered by depth, so the first
+//    are taken 64 at a time, one per lane (fewer: several lanes each), and the
+//    lanes walk their bucket's points from the nearest on.  Buckets are ordered by depth, so the first
 //    points of all of them are the front of what the rays meet: once more
 //    than 64 neighbours of each ray are known, points too deep to be among
 //    the 64 nearest are not visited any more, nor buckets behind them;
@@ -970,20 +970,29 @@ __device__ __forceinline__ void search_group(const RayGeom *rs, RaySlot *slot, S
             test_points(in, P);
         }
     };
-    // the points of one bucket per lane: slots at .. end - 1 (none: end <= at),
-    // depth bound zmax
-    auto sweep_buckets = [&](int at, int end, float zmax) {
+    // the points of `share` neighbouring lanes' bucket, each lane every share-th
+    // one from `at` on: slots up to end - 1 (none: end <= at), depth bound zmax;
+    // `first` on the first of a bucket's lanes.  What is left to too few lanes is
+    // flattened: below 12 where every lane has a bucket (visiting all buckets'
+    // front points first is worth more than the idle lanes), below 24 where few
+    // buckets are crowded (us, 12 / 24 / 32 / 44: K-NP of 1.5M points at 128x128
+    // 192 / 102 / 115 / 147, 192x192 112 / 117 / 108 / 95, 257x257 163 / 154 / 153 /
+    // 138; search at 128x128 111 / 107 / 111 / 140, 257x257 122 / 103 / 102 / 118).
+    auto sweep_buckets = [&](int at, int end, float zmax, int share, bool first) {
         uint64_t go = ballot(at < end);
-        while (popc64(go) >= 12) {
+        const int few = share > 1 ? 24 : 12;
+        while (popc64(go) >= few) {
             // (a lane without points left loads the table's first point)
             const float4 P = load_point(at < end ? at : 0);
             const uint64_t near = go & ballot(P.z <= __builtin_fminf(zmax, z_hi));
             test_points(near & ballot(P.z >= z_lo), P);
             // (points are ordered by depth: behind one too deep all are)
-            at = in_mask(near) ? at + 1 : end;
+            at = in_mask(near) ? at + share : end;
             go = ballot(at < end);
         }
-        if (go) sweep_flat(at, max(end - at, 0), true, zmax);
+        // (a bucket's lanes step together, so what is left of it follows its
+        // first lane's place)
+        if (go) sweep_flat(at, first ? max(end - at, 0) : 0, true, zmax);
     };
 
     const int wx0 = max(gx0 - h, 0), wx1 = min(gx1 + h, Wg - 1);
@@ -1109,16 +1118,22 @@ __device__ __forceinline__ void search_group(const RayGeom *rs, RaySlot *slot, S
             const int take = min(nbl, WAVE);
             nbl -= take;
             lds_sync();
+            // each to as many lanes as there are for it (a bucket per lane at any
+            // number of them left most lanes idle in the crowded windows of a
+            // low resolution, 18 buckets of 70 to 400 points for four rays:
+            // K-NP of 1.5M points at 257x257 336 us, 154 so, search 171 and 103)
+            const int share = (int)(((float)WAVE + 0.5f) * __builtin_amdgcn_rcpf((float)take));
+            const int own = (int)(((float)l + 0.5f) * __builtin_amdgcn_rcpf((float)share)), part = l - own * share;
             int at = 0, end = 0;
             float zmax = 0.0f;
-            if (l < take) {
-                const int2 e = sh.bl[nbl + l];
-                at = c.offsets[e.x];
+            if (own < take) {
+                const int2 e = sh.bl[nbl + own];
+                at = c.offsets[e.x] + part;
                 end = c.offsets[e.x + 1];
                 zmax = zmax_at(distance(wx0 + (e.y & 0xffff), wy0 + (int)((uint32_t)e.y >> 16), 0, 0));
             }
             lds_sync();
-            sweep_buckets(at, end, zmax);
+            sweep_buckets(at, end, zmax, share, part == 0);
         }
     }
 #pragma unroll
