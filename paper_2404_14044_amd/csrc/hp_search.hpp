@@ -124,16 +124,28 @@ constexpr int GROUP = 4;
 // cases.
 constexpr int HELD_WALK = 2 * WAVE;
 constexpr int HELD_KNP = WAVE;
-constexpr int HELD_SLAB = 8 * WAVE;
+constexpr int HELD_SLAB = 7 * WAVE;
 constexpr int BL_CAP = 3 * 64;  // listed buckets: a wave's worth, and two cells more
 
-// One wave's LDS while it searches G rays, holding HELD keys of each.
+// A slab of the multi-surface sampler's neighbours with their points.
+struct SlabList {
+    float4 nb_p[WAVE];
+    float nb_t[WAVE];
+};
+
+// One wave's LDS while it searches G rays, holding HELD keys of each.  A slab is
+// read only between searches, in the place of what a search alone needs.
 template <int G, int HELD>
 struct SearchScratch {
     uint64_t pend[G][HELD + WAVE];  // keys of the neighbours found so far
-    int2 bl[BL_CAP];             // listed buckets: key, offset from the window's corner (16 bits each)
-    int2 cl[WAVE];               // listed depth cells: first bucket in the window, width and prefix (16 bits each)
-    int32_t head[WAVE];          // (indexed by flat point offset within a sweep step)
+    union {
+        struct {
+            int2 bl[BL_CAP];     // listed buckets: key, offset from the window's corner (16 bits each)
+            int2 cl[WAVE];       // listed depth cells: first bucket in the window, width and prefix (16 bits each)
+            int32_t head[WAVE];  // (indexed by flat point offset within a sweep step)
+        };
+        SlabList slab;
+    };
 };
 
 // The rays a wave holds between search and walk.
@@ -185,20 +197,15 @@ struct KnpLds {
 };
 static_assert(sizeof(KnpLds) <= 7680, "K-NP LDS above 7680 B costs occupancy");
 
-// The multi-surface sampler: one ray's neighbours, and a slab of 64 of them at
-// a time with their points.
-struct SlabList {
-    float4 nb_p[WAVE];
-    float nb_t[WAVE];
-};
-
+// The multi-surface sampler: one ray's neighbours, a slab of 64 of them at a time
+// with their points.
 struct SlabLds {
     RayGeom rs[RS_CAP];
     RaySlot slot[1];
     SearchScratch<1, HELD_SLAB> s;
-    SlabList list;
 };
-static_assert(sizeof(SlabLds) <= 10240, "slab LDS above 10240 B costs occupancy");
+// (20 waves of a CU; see k_search_ms)
+static_assert(sizeof(SlabLds) <= 7680, "slab LDS above 7680 B costs occupancy");
 
 // Rays per XCD band: two image rows of an 800-pixel-wide view (object view
 // 0.568 ms with bands of 12,800 rays, 0.545 with 3,200, 0.532 with 1,600,
@@ -231,7 +238,7 @@ inline bool dealt(const SearchCtx &c) { return c.blocks <= 0 && c.n_rays > DEALT
 // 450 pixels 172 / 130 / 102; search and render in one, whose CUs' shares are
 // fixed, 119 / 138 / 191, 149 / 187 / 215, 180 / 174 / 247, 299 / 252 / 250).
 // The multi-surface sampler takes its rays one at a time, each for long
-// (640k rays, 400 positions 2268 / 2486 / 3271; 160k rays 795 / 1309 / 2129).
+// (640k rays, 400 positions 1970 / 2437 / 3290; 160k rays, 200 positions 587 / 761 / 1107).
 enum SearchKind { SEARCH_WALK, SEARCH_KNP, SEARCH_FUSED };
 
 inline int32_t default_chunk(const SearchCtx &c, SearchKind kind)
@@ -660,14 +667,16 @@ __device__ __forceinline__ void for_each_group_banded(RayGeom *rs, int *take, Gr
         r0 = ch * chunk;
         n = (int)min(chunk, n_rays - r0);
     };
-    // its share of them, in passes of up to four (the chunks themselves stay
-    // small, for balance)
+    // its share of them, up to four at a time (the chunks themselves stay
+    // small, for balance), or RS_CAP rays' worth where none is searched with
+    // its neighbours
     const uint32_t mine = slot < my_chunks ? (my_chunks - slot + n_slots - 1) / n_slots : 0;
+    const uint32_t most = MAXG == 1 && NW == 1 && chunk < 4 ? RS_CAP / chunk : 4;
     for (uint32_t at = 0;;) {
-        uint32_t per = 4;
+        uint32_t per = most;
         const int l = phase_lane_id();
         if constexpr (NW > 1) {
-            per = min(max((mine - at) / (2 * NW), 1u), 4u);
+            per = min(max((mine - at) / (2 * NW), 1u), most);
             int j = 0;
             if (l == 0) j = atomicAdd(take, (int)per);
             at = (uint32_t)uniform_i32(j);
@@ -676,28 +685,15 @@ __device__ __forceinline__ void for_each_group_banded(RayGeom *rs, int *take, Gr
         const uint32_t li = slot + at * n_slots;
         if constexpr (NW == 1) at += per;
         const SearchCtx c = phase_ctx();
-        uint32_t ra, rb, rc, rd;
-        int na, nb, nc, nd;
-        chunk_rays(li, ra, na);
-        chunk_rays(per > 1 ? li + n_slots : ~0u, rb, nb);
-        chunk_rays(per > 2 ? li + 2 * n_slots : ~0u, rc, nc);
-        chunk_rays(per > 3 ? li + 3 * n_slots : ~0u, rd, nd);
-        const int nab = na + nb, nabc = nab + nc, ntot = nabc + nd;
-        auto ray_at = [&](int i) -> int64_t {
-            const uint32_t r = i < na ? ra + i : i < nab ? rb + (i - na) : i < nabc ? rc + (i - nab) : rd + (i - nabc);
-            return (int64_t)r;
-        };
-        for (int s0 = 0; s0 < ntot; s0 += RS_CAP) {
-            const int n = min(RS_CAP, ntot - s0);
-            // lanes 4 k .. 4 k + 3 set up ray s0 + k (lanes past the batch
-            // repeat its last ray)
-            const int k = l / RS_LANES, sub = l % RS_LANES;
-            const int64_t rk = ray_at(s0 + (k < n ? k : n - 1));
+        // n rays of a pass, lanes 4 k .. 4 k + 3 set up the k-th, ray rk (lanes
+        // past the pass repeat its last ray)
+        const int k = l / RS_LANES, sub = l % RS_LANES;
+        auto pass = [&](uint32_t rk, int n) {
             const float z1 = ray_first_zmin(c, c.ray0 + rk, sub);
             const bool lead = sub == 0 && k < n;
             const uint64_t near = ballot(lead && z1 < __builtin_inff());  // bit RS_LANES k
-            if (lead && !(z1 < __builtin_inff())) empty(rk);
-            if (near == 0) continue;
+            if (lead && !(z1 < __builtin_inff())) empty((int64_t)rk);
+            if (near == 0) return;
             lds_sync();
             int u;
             const RayGeom gk = ray_setup(c, c.ray0 + rk, sub, z1, u);
@@ -711,7 +707,34 @@ __device__ __forceinline__ void for_each_group_banded(RayGeom *rs, int *take, Gr
                 const int i = __builtin_ctzll(todo) / RS_LANES;
                 const int m = group_size(joined, i, MAXG);
                 todo &= ~(((1ull << (RS_LANES * m)) - 1ull) << (RS_LANES * i));
-                groups(m, (int)ray_at(s0 + i), i, todo == 0);
+                groups(m, readlane_i32((int)rk, RS_LANES * i), i, todo == 0);
+            }
+        };
+        if constexpr (MAXG == 1) {
+            for (uint32_t s0 = 0; s0 < per * chunk; s0 += RS_CAP) {
+                // the k-th ray of these chunks (those past the last one follow all others)
+                const uint32_t i = s0 + k;
+                const uint32_t j = (uint32_t)(((float)i + 0.5f) * __builtin_amdgcn_rcpf((float)chunk));
+                uint32_t r;
+                int have;
+                chunk_rays(j < per ? li + j * n_slots : ~0u, r, have);
+                r += i - j * chunk;
+                const bool in = (int)(i - j * chunk) < have;
+                const int n = popc64(ballot(in)) / RS_LANES;
+                if (n == 0) break;
+                pass(in ? r : (uint32_t)readlane_i32((int)r, RS_LANES * (n - 1)), n);
+            }
+        } else {
+            uint32_t ra, rb, rc, rd;
+            int na, nb, nc, nd;
+            chunk_rays(li, ra, na);
+            chunk_rays(per > 1 ? li + n_slots : ~0u, rb, nb);
+            chunk_rays(per > 2 ? li + 2 * n_slots : ~0u, rc, nc);
+            chunk_rays(per > 3 ? li + 3 * n_slots : ~0u, rd, nd);
+            const int nab = na + nb, nabc = nab + nc, ntot = nabc + nd;
+            for (int s0 = 0; s0 < ntot; s0 += RS_CAP) {
+                const int n = min(RS_CAP, ntot - s0), i = s0 + min(k, n - 1);
+                pass(i < na ? ra + i : i < nab ? rb + (i - na) : i < nabc ? rc + (i - nab) : rd + (i - nabc), n);
             }
         }
     }
@@ -1779,7 +1802,8 @@ __device__ __forceinline__ void first_slab(SlabLds &lds, SlabKeys &k, int rec)
         lds_sync();
         return;
     }
-    constexpr int R = HELD_SLAB / WAVE;
+    constexpr int R = HELD_SLAB / WAVE + 1;
+    static_assert(R == 8, "the keys held and their room for 64 more are sorted together");
     uint64_t x[R];
 #pragma unroll
     for (int e = 0; e < R; ++e) x[e] = WAVE * e + l < held ? lds.s.pend[0][WAVE * e + l] : KEY_NONE;
@@ -1813,7 +1837,7 @@ __device__ __forceinline__ int uniform_samples(const RayGeom &g, SlabLds &lds, S
 {
     const SearchCtx c = phase_ctx();
     const int l = lane_id();
-    SlabList &sh = lds.list;
+    SlabList &sh = lds.s.slab;
     first_idx = -1;
     if (slab.rest == 0) return 0;
     const int nk = c.ms_steps;

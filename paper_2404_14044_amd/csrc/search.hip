@@ -160,10 +160,27 @@ k_search_sample(SearchCtx, SampleOut)
     search_sample_body<KT, NW>();
 }
 
+// Bound by the latency of short chains (bisections in the LDS, gathers of a slab's
+// points), so five waves per SIMD with lists of up to 8, though those of 5 to 8
+// spill 20 registers for it (200 positions, us, four / five waves: room of 500k points
+// 900x900 6356 / 5973, plane of 5k 1371 / 1261, object cloud of 1M 1921 / 2028).
 template <int KT>
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(KT <= 16 ? 4 : 2, 8))) k_search_ms(SearchCtx, SampleOut)
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(KT <= 8 ? 5 : KT <= 16 ? 4 : 2, 8)))
+k_search_ms(SearchCtx, SampleOut)
 {
     search_ms_body<KT>();
+}
+
+// The multi-surface sampler's single rays: few enough waves that one set-up pass
+// of a wave serves about twelve rays, enough to fill the GPU (200 positions, us, by
+// waves 65,536 / 24,576 / 16,384: object cloud of 1M points 300x300 443 / 431 / 459,
+// 600x600 894 / 901 / 955, 900x900 1915 / 2212 / 2180; plane of 200k 300x300 174 /
+// 141 / 135, 600x600 445 / 421 / 472, 900x900 897 / 935 / 955).
+static int64_t ms_grid(const SearchCtx &c)
+{
+    if (c.blocks > 0 || c.chunk > 1) return wave_grid(c);
+    const int64_t waves = c.n_rays / 12;
+    return banded_grid(c, waves < 16384 ? 16384 : waves < WAVE_BLOCKS ? waves : WAVE_BLOCKS);
 }
 
 template <int KT>
@@ -175,7 +192,7 @@ static void launch_search_k(const SearchCtx &c, const SampleOut &o, hipStream_t 
         k_search_sample<KT, NW><<<dim3((unsigned)blocks), dim3(WAVE * NW), 0, s>>>(c, o);
         return;
     }
-    const int64_t blocks = wave_grid(c);
+    const int64_t blocks = c.sampler == HP_SAMPLER_MS ? ms_grid(c) : wave_grid(c);
     if (blocks == 0) return;
     const dim3 grid((unsigned)blocks), block(WAVE);
     if (c.sampler == HP_SAMPLER_MS) k_search_ms<KT><<<grid, block, 0, s>>>(c, o);
