@@ -119,8 +119,8 @@ typedef struct hp_camera {
  *  flags: reserved, must be 0.
  *  search_chunk: rays a search workgroup takes at a time, 0 = default (1 to 4 by
  *      the number of rays), at most 64; search_blocks: search grid (waves
- *      each taking chunks of rays in turn), 0 = default (by the number of
- *      rays).
+ *      each taking chunks of rays in turn; workgroups in hp_search_render, at
+ *      most one per CU), 0 = default (by the number of rays).
  *      Neither changes any result; an autotuner picks them per workload.
  *  radius_mode: HP_RADIUS_*.  In the Eq. 3 modes rho(t) = kappa t with, for
  *      the pixel centre E = (a, b, 1) on the image plane at unit focal

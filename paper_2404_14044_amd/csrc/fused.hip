@@ -293,7 +293,11 @@ template <int KT, int PREC, bool MS>
 static void launch_fused_kpm(const SearchCtx &c, const FusedArgs &a, hipStream_t s)
 {
     constexpr int NW = fused_waves<KT, PREC, MS>();
-    const int64_t blocks = banded_grid(c, c.blocks > 0 ? (c.blocks + NW - 1) / NW : CU_BLOCKS);
+    // (never more than one workgroup per CU, whatever grid the caller names: each
+    // loads the decoder, and a second one waits for the first to drain; frames of
+    // the object with 65,536 named, us, that many waves / one workgroup per CU:
+    // 192x192 643 / 129, 400x400 809 / 206, 800x800 888 / 437)
+    const int64_t blocks = banded_grid(c, c.blocks > 0 && c.blocks < CU_BLOCKS ? c.blocks : CU_BLOCKS);
     if (blocks == 0) return;
     k_fused<KT, PREC, MS><<<dim3((unsigned)blocks), dim3(WAVE * NW), 0, s>>>(c, a);
 }
