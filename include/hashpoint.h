@@ -118,7 +118,8 @@ typedef struct hp_camera {
  *      mentions a Z-order arrangement; read here as an order of buckets).
  *  flags: reserved, must be 0.
  *  search_chunk: rays a search workgroup takes at a time, 0 = default (1 to 4 by
- *      the number of rays), at most 64; search_blocks: search grid (waves
+ *      the number of rays, also taken in place of a smaller one by searches of
+ *      more than 16,384 rays), at most 64; search_blocks: search grid (waves
  *      each taking chunks of rays in turn; workgroups in hp_search_render, at
  *      most one per CU), 0 = default (by the number of rays).
  *      Neither changes any result; an autotuner picks them per workload.

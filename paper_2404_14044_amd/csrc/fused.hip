@@ -318,7 +318,7 @@ static void launch_fused_k(const SearchCtx &c, const FusedArgs &a, int precision
 hipError_t launch_fused(const SearchCtx &ctx, const FusedArgs &a, int kt, int precision, hipStream_t s)
 {
     SearchCtx c = ctx;
-    if (c.chunk <= 0) c.chunk = default_chunk(c, SEARCH_FUSED);
+    c.chunk = launch_chunk(c, SEARCH_FUSED);
     if (kt == 4) launch_fused_k<4>(c, a, precision, s);
     else if (kt == 8) launch_fused_k<8>(c, a, precision, s);
     else launch_fused_k<16>(c, a, precision, s);

@@ -231,12 +231,18 @@ inline bool dealt(const SearchCtx &c) { return c.blocks <= 0 && c.n_rays > DEALT
 // Rays per work chunk where the caller names none.  Neighbouring rays are
 // searched together, so a chunk of four is the cheapest by ray; a launch of few
 // rays leaves most of the GPU idle that way, or waiting for the few waves that
-// drew four crowded rays, and is better split further (us by rays per chunk
-// 1 / 2 / 4; object cloud of 1M points, squares of 64, 192, 256, 350 and 500
-// pixels: search 105 / - / 227, 143 / 110 / 145, 176 / 116 / 102, 251 / 161 / 118,
-// 442 / 317 / 241; K-NP 55 / - / -, 77 / 72 / 284, 101 / 78 / 99, 136 / 90 / 79,
-// 450 pixels 172 / 130 / 102; search and render in one, whose CUs' shares are
-// fixed, 119 / 138 / 191, 149 / 187 / 215, 180 / 174 / 247, 299 / 252 / 250).
+// drew four crowded rays, and is better split further.  The limits are those of
+// the cloud whose rays differ most, an object's; a room or a plane, whose rays
+// are alike, would take four earlier (us by rays per chunk 1 / 2 / 4.
+// Object cloud of 1M points, squares of 64, 192, 256, 350 pixels: search 48 / 77 /
+// 179, 102 / 75 / 116, 134 / 94 / 102, 199 / 129 / 94; K-NP 56 / 94 / 194, 76 / 71 /
+// 139, 98 / 77 / 98, 136 / 90 / 80; search and render in one, whose CUs' shares are
+// fixed, 64, 192, 400: 55 / 85 / 188, 106 / 103 / 129, 219 / 193 / 206.
+// Room of 2M points, 64, 192, 256: search 107 / 140 / 340, 236 / 145 / 164, 366 / 214 /
+// 150; K-NP 98 / 132 / 309, 193 / 122 / 145, 282 / 182 / 140; in one, 64, 192, 400:
+// 130 / 151 / 355, 272 / 226 / 225, 878 / 667 / 568.
+// Plane of 200k points, 64, 192: search 18 / 17 / 22, 93 / 54 / 34; K-NP 15 / 14 / 18,
+// 73 / 42 / 27; in one, 64, 192, 400: 27 / 24 / 30, 71 / 62 / 50, 193 / 148 / 129).
 // The multi-surface sampler takes its rays one at a time, each for long
 // (640k rays, 400 positions 1970 / 2437 / 3290; 160k rays, 200 positions 587 / 761 / 1107).
 enum SearchKind { SEARCH_WALK, SEARCH_KNP, SEARCH_FUSED };
@@ -247,6 +253,23 @@ inline int32_t default_chunk(const SearchCtx &c, SearchKind kind)
     const int64_t one = kind == SEARCH_FUSED ? 65536 : 6144;
     const int64_t two = kind == SEARCH_FUSED ? 196608 : kind == SEARCH_KNP ? 65536 : 49152;
     return c.n_rays <= one ? 1 : c.n_rays <= two ? 2 : 4;
+}
+
+// Rays per work chunk of a launch.  A chunk named by the caller that is smaller
+// than the default is raised to it in launches of many rays: it would leave
+// neighbours to different waves, and a ray searched alone takes longer than
+// its share of a group and than it took when there were none (search, us, by
+// rays per chunk 1 / default, in brackets 1 before rays were searched together:
+// plane of 200k points 256x256 137 / 49 [98], 500x500 261 / 148 [240]; object cloud of
+// 1M points 350x350 199 / 99 [145], 500x500 294 / 175 [239]; K-NP of the plane
+// 256x256 108 / 60 [86]).  Launches of up to 16,384 rays take what they are given,
+// for which there are reasons either way (K-NP of the object cloud 100x100 44 / 65
+// [49], search of the plane 100x100 35 / 24 [27]).
+inline int32_t launch_chunk(const SearchCtx &c, SearchKind kind)
+{
+    const int32_t own = default_chunk(c, kind);
+    if (c.chunk <= 0) return own;
+    return kind != SEARCH_FUSED && c.n_rays > 16384 && c.chunk < own ? own : c.chunk;
 }
 
 // Grid of a search launch: at most `most` workgroups, a multiple of 8.

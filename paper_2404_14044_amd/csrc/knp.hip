@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(WAVE *NW) __attribute__((amdgpu_waves_per_eu(4
 hipError_t launch_knp(const SearchCtx &ctx, const KnpArgs &a, hipStream_t s)
 {
     SearchCtx c = ctx;
-    if (c.chunk <= 0) c.chunk = default_chunk(c, SEARCH_KNP);
+    c.chunk = launch_chunk(c, SEARCH_KNP);
     const int64_t blocks = dealt(c) ? banded_grid(c, CU_BLOCKS) : wave_grid(c);
     if (blocks == 0) return hipSuccess;
     if (dealt(c)) k_knp<KNP_WAVES><<<dim3((unsigned)blocks), dim3(WAVE * KNP_WAVES), 0, s>>>(c, a);

@@ -202,7 +202,7 @@ static void launch_search_k(const SearchCtx &c, const SampleOut &o, hipStream_t 
 hipError_t launch_search_sample(const SearchCtx &ctx, const SampleOut &o, int kt, hipStream_t s)
 {
     SearchCtx c = ctx;
-    if (c.chunk <= 0) c.chunk = default_chunk(c, SEARCH_WALK);
+    c.chunk = launch_chunk(c, SEARCH_WALK);
     switch (kt) {
     case 4: launch_search_k<4>(c, o, s); break;
     case 8: launch_search_k<8>(c, o, s); break;
