@@ -18,7 +18,8 @@ of one dimension tried with the others at their best so far, dimensions in
 turn, twice over), so a workload costs a few dozen timed frames, not the
 product of the ranges.  Results are cached by workload shape in an explicit
 cache object that can be saved to and loaded from JSON; each entry keeps the
-default and the tuned frame time and every trial.
+default and the tuned frame time and every trial.  Entries measured before the
+library's launches last changed (SHAPES) are measured again.
 """
 from __future__ import annotations
 
@@ -43,6 +44,12 @@ SPACE = {
 DEFAULTS = {"layout": hp.HP_LAYOUT_ROWMAJOR, "search_chunk": 0, "search_blocks": 0,
             "search_band": 1600, "window_shape": hp.HP_WINDOW_DISC, "render_rays": 0,
             "render_blocks": 0}
+# What the launch shapes mean to the library: raised when its launches change, so
+# that choices measured on others are measured again.  (Entries without it
+# spell out the former defaults, search_chunk 4, search_blocks 65536 and
+# render_rays 16, which now turn off what the library does by itself at 0:
+# a frame of 64x64 rays of a 1M-point object 940 us by default, 1,074 so.)
+SHAPES = 2
 
 
 def shape_key(cams: Sequence, params, n_points: int, precision: int) -> str:
@@ -105,8 +112,9 @@ class Autotuner:
              space: Optional[Dict[str, Sequence[int]]] = None, rounds: int = 2):
         """Return params with the fastest layout and launch shapes found."""
         key = shape_key(cams, params, xyz.shape[0], precision)
-        if key in self.cache:
-            return params.replace(**self.cache[key]["best"])
+        known = self.entry(xyz, cams, params, precision)
+        if known is not None:
+            return params.replace(**known["best"])
         space = dict(space or SPACE)
         best = {k: DEFAULTS[k] for k in space}
         trials = []
@@ -139,10 +147,11 @@ class Autotuner:
         if default_ms <= best_ms:
             best, best_ms = default_cfg, default_ms
         self.cache[key] = {"best": best, "ms": best_ms, "default_ms": default_ms,
-                           "trials": trials}
+                           "trials": trials, "shapes": SHAPES}
         self.save()
         return params.replace(**best)
 
     def entry(self, xyz, cams, params, precision: int = hp.HP_BF16) -> Optional[dict]:
-        """The cached result for this workload, if it was tuned."""
-        return self.cache.get(shape_key(cams, params, xyz.shape[0], precision))
+        """The cached result for this workload, if it was tuned with these launch shapes."""
+        found = self.cache.get(shape_key(cams, params, xyz.shape[0], precision))
+        return found if found is not None and found.get("shapes") == SHAPES else None
