@@ -233,7 +233,7 @@ inline bool dealt(const SearchCtx &c) { return c.blocks <= 0 && c.n_rays > DEALT
 // rays leaves most of the GPU idle that way, or waiting for the few waves that
 // drew four crowded rays, and is better split further.  The limits are those of
 // the cloud whose rays differ most, an object's; a room or a plane, whose rays
-// are alike, would take four earlier (us by rays per chunk 1 / 2 / 4.
+// are alike, takes four earlier (us by rays per chunk 1 / 2 / 4.
 // Object cloud of 1M points, squares of 64, 192, 256, 350 pixels: search 48 / 77 /
 // 179, 102 / 75 / 116, 134 / 94 / 102, 199 / 129 / 94; K-NP 56 / 94 / 194, 76 / 71 /
 // 139, 98 / 77 / 98, 136 / 90 / 80; search and render in one, whose CUs' shares are
@@ -252,6 +252,11 @@ inline int32_t default_chunk(const SearchCtx &c, SearchKind kind)
     if (c.sampler == HP_SAMPLER_MS && kind != SEARCH_KNP) return 1;
     const int64_t one = kind == SEARCH_FUSED ? 65536 : 6144;
     const int64_t two = kind == SEARCH_FUSED ? 196608 : kind == SEARCH_KNP ? 65536 : 49152;
+    // (a cloud of few points per ray has no crowded rays to wait for: search / K-NP
+    // of a plane of 200k points by rays per chunk 2 / 4, 200x200 65 / 39, 51 / 32,
+    // 220x220 68 / 42, 55 / 35; object cloud of 100k 200x200 64 / 51, 44 / 37, but
+    // 128x128 47 / 66, 57 / 72 and 150x150 48 / 56, 35 / 38)
+    if (kind != SEARCH_FUSED && c.n_rays > 24576 && c.n_points * c.n_views < 8 * c.n_rays) return 4;
     return c.n_rays <= one ? 1 : c.n_rays <= two ? 2 : 4;
 }
 

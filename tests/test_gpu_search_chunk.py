@@ -1,5 +1,6 @@
-"""Chunks smaller than the default in launches of many rays: the default's results in
-its time, though the caller names single rays."""
+"""The rays a wave takes at a time: in launches of many rays, chunks smaller than the
+default give its results in its time, though the caller names single rays; and
+the default of a sparse cloud is as fast as any."""
 import numpy as np
 import pytest
 import torch
@@ -12,32 +13,59 @@ from test_gpu_search_launches import _same, _valid
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("op", ["search", "blend"])
-@pytest.mark.parametrize("W,H", [(129, 128), (256, 255), (500, 501)])
-@pytest.mark.parametrize("chunk", [1, 2, 3])
-def test_small_chunks(W, H, chunk, op):
+def _sheet(W, H):
+    """200k points on a sheet that fills the view."""
     cam = scenes.pinhole(W, H, 60.0, np.eye(3), np.zeros(3))
     rng = np.random.default_rng(5)
     xy = rng.uniform(-1, 1, (200_000, 2)) * np.array([W, H]) / 2 / cam.fx
     z = rng.uniform(4.5, 4.52, (200_000, 1))
     xyz = torch.from_numpy(np.concatenate([xy * z, z], 1).astype(np.float32)).cuda()
     colors = torch.from_numpy(scenes.point_colors(200_000, 3)).cuda()
-    p = scenes.default_params(0.02, 1.5, 10.0, K=8, S=16)
+    return cam, xyz, colors, scenes.default_params(0.02, 1.5, 10.0, K=8, S=16)
+
+
+def _time(run):
+    best = float("inf")
+    for _ in range(8):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(4):
+            run()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("op", ["search", "blend"])
+@pytest.mark.parametrize("layout", [0, 2])
+def test_sparse_clouds(layout, op):
+    """200 x 200 rays, five points each: two rays at a time took 1.5 times as long as
+    four."""
+    cam, xyz, colors, p = _sheet(200, 200)
+    p = p.replace(layout=layout)
+    tab = hp.build_table(xyz, [cam], p)
+    times = {}
+    for chunk in (0, 2, 4, 8):
+        q = p.replace(search_chunk=chunk)
+        out = hp.alloc_samples(tab.n_rays, q, xyz.device)
+        times[chunk] = _time((lambda: hp.search_sample(tab, q, out=out)) if op == "search" else
+                             (lambda: hp.knp_blend(tab, q, 8, colors)))
+    print(op, times)
+    assert times[0] <= 1.15 * times[4], times
+
+
+@pytest.mark.parametrize("op", ["search", "blend"])
+@pytest.mark.parametrize("W,H", [(129, 128), (256, 255), (500, 501)])
+@pytest.mark.parametrize("chunk", [1, 2, 3])
+def test_small_chunks(W, H, chunk, op):
+    cam, xyz, colors, p = _sheet(W, H)
     tab = hp.build_table(xyz, [cam], p)
     outs, times = [], []
     for q in (p, p.replace(search_chunk=chunk)):
         run = (lambda: hp.search_sample(tab, q)) if op == "search" else (lambda: hp.knp_blend(tab, q, 8, colors))
         outs.append(_valid(run(), 8) if op == "search" else run())
-        best = float("inf")
-        for _ in range(8):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            for _ in range(4):
-                run()
-            b.record()
-            torch.cuda.synchronize()
-            best = min(best, a.elapsed_time(b))
-        times.append(best)
+        times.append(_time(run))
     print(op, W, H, chunk, times)
     _same(*outs)
     # (single rays took 1.5 to 2.7 times the default's time)
