@@ -147,10 +147,11 @@ __device__ __forceinline__ void search_ms_body()
     }, [&](int64_t ray) { put_empty(ray); });
 }
 
-// 4 waves per SIMD (128 VGPRs, no spill with lists of up to 8), 2 with lists
-// of 32.  A kernel whose waves own scratch memory is slower to launch waves and
-// slower in all: at 5 waves with spills the room view's 16-entry lists measured
-// 2.78 against 2.55 ms.
+// 4 waves per SIMD (128 VGPRs), 2 with lists of 32.  Lists of up to 8 do not spill
+// at 4; those of 9 to 16 spill about ten registers, which costs less than a wave
+// per SIMD does (4 waves / 3 without a spill, us: room of 5M points,
+// lists of 16, 900x900 1310 / 1447, of 1M points, lists of 12, 400x400 357 / 421; 64x64
+// equal).
 constexpr int search_waves(int kt) { return kt <= 16 ? 16 : 8; }  // per workgroup that fills a CU
 
 template <int KT, int NW>
