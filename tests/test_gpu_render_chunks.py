@@ -1,0 +1,69 @@
+"""Rays per render chunk by default: never much slower than chunks of sixteen rays,
+where all rays are alike, and the same results on both sides of each limit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2404_14044_amd import hashpoint as hp
+from paper_2404_14044_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+def _samples(R, S, K, n):
+    """S samples for every ray, of neighbours near each other in the cloud."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S)
+    t = (1.0 + torch.rand(R, S, generator=gen, device="cuda")).sort(1).values
+    near = (torch.arange(R, device="cuda") * n // R)[:, None, None]
+    idx = (near + torch.randint(0, 64, (R, S, K), generator=gen, device="cuda")) % n
+    dist = (0.01 + 0.1 * torch.rand(R, S, K, generator=gen, device="cuda")).sort(2).values
+    return {"n_sel": torch.full((R,), S, dtype=torch.int32, device="cuda"), "t": t.reshape(-1).contiguous(),
+            "knn_idx": idx.to(torch.int32).reshape(-1).contiguous(), "knn_dist": dist.reshape(-1).contiguous()}
+
+
+def _setup(R, S, K=8, n=200_000):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    feat = torch.randn(n, 32, generator=gen, device="cuda")
+    mlp = hp.to_device_mlp(scenes.make_mlp(3), "cuda")
+    p = scenes.default_params(0.05, 1.0, 4.0, K=K, S=S)
+    out = {"rgb": torch.empty(3 * R, device="cuda"), "depth": torch.empty(R, device="cuda"),
+           "acc": torch.empty(R, device="cuda")}
+    smp = _samples(R, S, K, n)
+
+    def run(rays, prec):
+        return hp.render(smp, R, feat, mlp, p.replace(render_rays=rays), prec, out=out)
+    return run
+
+
+@pytest.mark.parametrize("prec", [hp.HP_FP32, hp.HP_BF16])
+@pytest.mark.parametrize("R", [49_152, 49_153, 98_304, 98_305])
+@pytest.mark.parametrize("S", [8, 9, 16, 17])
+def test_results_on_both_sides_of_the_limits(R, S, prec):
+    run = _setup(R, S)
+    want = {k: v.clone() for k, v in run(16, prec).items()}
+    got = run(0, prec)
+    for k, v in want.items():
+        assert torch.equal(v.view(torch.int32), got[k].view(torch.int32)), k
+
+
+@pytest.mark.parametrize("prec,S", [(hp.HP_BF16, 8), (hp.HP_BF16, 16), (hp.HP_FP32, 8), (hp.HP_FP32, 16),
+                                    (hp.HP_BF16, 32)])
+@pytest.mark.parametrize("side", [128, 221, 256, 313])
+def test_time_of_full_rays(side, prec, S):
+    """Chunks of four rays took up to 1.2 times as long as chunks of sixteen from
+    256 x 256 rays of 8 samples on (1.3 in a room, whose neighbours are cached)."""
+    run, times = _setup(side * side, S), {}
+    for rays in (0, 16):
+        times[rays] = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(6):
+                run(rays, prec)
+            b.record()
+            torch.cuda.synchronize()
+            times[rays] = min(times[rays], a.elapsed_time(b) / 6e-3)
+    print(side, prec, S, times)
+    assert times[0] <= 1.1 * times[16], times
