@@ -315,17 +315,18 @@ static void launch_render_rpw(const RenderArgs &a, int precision, int64_t blocks
 // for less time, in launches of few rays.  How few depends on what 16 would take:
 // up to 16 samples a ray the shared-weights kernel, 768 workgroups of which (98,304
 // rays) are resident at once and end together where all rays are alike; with
-// more, or with the FP32 decoder and more than 8, each chunk is long enough for
+// more, or with the FP32 decoder and more than 11, each chunk is long enough for
 // its share to matter more (render alone, us, 16 / 4 rays per chunk.
 // BF16, 16 samples: room of 5M points 200x200 76 / 56, 220x220 77 / 66, 256x256 81 /
 // 88, 313x313 102 / 125; object cloud of 1M 220x220 50 / 32, 256x256 53 / 48, 313x313
 // 62 / 51.  BF16, 8 samples: 42 / 38, 43 / 51, 54 / 71; 33 / 23, 34 / 35, 42 / 37 (220,
 // 256, 313).  FP32, 8 samples: 90 / 75, 93 / 100, 132 / 144; 57 / 40, 58 / 61, 90 / 66.
-// FP32, 16 samples: room 256x256 175 / 177, 313x313 260 / 256, object 88 / 87, 124 / 94.
+// FP32, room 256x256, 10 and 12 samples: 115 / 136, 136 / 139; 16 samples: room 256x256
+// 175 / 177, 313x313 260 / 256, object 88 / 87, 124 / 94.
 // BF16, 32 samples: 191 / 154, 237 / 211; 88 / 77, 96 / 76; 400x400 FP32 211 / 223).
 static int64_t few_rays(const RenderArgs &a, int precision)
 {
-    return a.S <= (precision == HP_BF16 ? 16 : 8) ? 49152 : 98304;
+    return a.S <= (precision == HP_BF16 ? 16 : 11) ? 49152 : 98304;
 }
 constexpr int FEW_RPW = 4;
 static_assert(SHARED_WAVES * FEW_RPW * HP_MAX_SAMPLES * sizeof(float4) <= SHARED_DYN_MAX,

@@ -39,7 +39,7 @@ def _setup(R, S, K=8, n=200_000):
 
 @pytest.mark.parametrize("prec", [hp.HP_FP32, hp.HP_BF16])
 @pytest.mark.parametrize("R", [49_152, 49_153, 98_304, 98_305])
-@pytest.mark.parametrize("S", [8, 9, 16, 17])
+@pytest.mark.parametrize("S", [8, 11, 12, 16, 17])
 def test_results_on_both_sides_of_the_limits(R, S, prec):
     run = _setup(R, S)
     want = {k: v.clone() for k, v in run(16, prec).items()}
@@ -48,7 +48,7 @@ def test_results_on_both_sides_of_the_limits(R, S, prec):
         assert torch.equal(v.view(torch.int32), got[k].view(torch.int32)), k
 
 
-@pytest.mark.parametrize("prec,S", [(hp.HP_BF16, 8), (hp.HP_BF16, 16), (hp.HP_FP32, 8), (hp.HP_FP32, 16),
+@pytest.mark.parametrize("prec,S", [(hp.HP_BF16, 8), (hp.HP_BF16, 16), (hp.HP_FP32, 8), (hp.HP_FP32, 10), (hp.HP_FP32, 16),
                                     (hp.HP_BF16, 32)])
 @pytest.mark.parametrize("side", [128, 221, 256, 313])
 def test_time_of_full_rays(side, prec, S):
