@@ -14,8 +14,8 @@
 // kernel to two waves per SIMD, and a tile per ray was a fifth full.  One
 // workgroup per CU, its waves dealing out its rays among themselves: a second
 // workgroup to replace it, let alone four, leaves the CU idle while the first
-// drains (425, 507, 540 us).  Frame of 640k rays of the object, BF16: 1,518 us
-// with one-wave workgroups, 425 here (the separate calls 317 + 188).
+// drains (425, 507, 540 us).  Frame of 640k rays of the object cloud, BF16: 1,511 us
+// with one-wave workgroups, 428 here (the separate calls 283 + 179).
 #include <type_traits>
 
 #include "hp_kernels.hpp"

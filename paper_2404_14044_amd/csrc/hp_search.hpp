@@ -39,10 +39,10 @@
 // within the first sixteen.
 //
 // The kernels are bound by instruction issue, vector and scalar, not by
-// memory (object view, 640k rays, 1M points: 1.0 TB/s).  One ray at a time,
-// with sorted lists kept by merging and four lanes to a candidate, took 285M
-// vector and 112M scalar instructions and 0.490 ms there; this way it takes
-// 0.317 ms (room view, 762k rays, 5M points: 2.79 -> 1.35 ms).
+// memory (object view, 640k rays, 1M points: 1.6 TB/s).  One ray at a time,
+// with sorted lists kept by merging and four lanes to a candidate, took 309M
+// vector and 123M scalar instructions and 0.509 ms there; this way it takes
+// 157M, 63M and 0.340 ms (room view, 762k rays, 5M points: 2.82 and 1.32 ms).
 #pragma once
 #include "hp_device.hpp"
 
@@ -853,9 +853,10 @@ __device__ __forceinline__ uint32_t keep_smallest(uint64_t *pend, int &n, int wa
 // as runs of consecutive table slots, one lane per run.
 // K-NP, which meets a ray's points in no order of depth and so must test nearly
 // all of its window anyway, takes the runs of windows ten times as crowded
-// (K-NP of a 350x350 view of the object 79 against 178 us, of 800x800 209
-// against 234; from 6,400 points on, windows of a room seen at 64x64, the
-// depth bound by distance drops more than that costs: 103 against 584 us).
+// (us, by limit 640 / 3,200 / 6,400: K-NP of the object cloud of 1M points at
+// 350x350 92 / 93 / 81, 500x500 147 / 126 / 113, 800x800 236 / 211 / 210; a room of 5M,
+// whose windows are deeper, gives some of it back, 350x350 155 / 169 / 215, 800x800
+// 678 / 681 / 681; without a limit a room of 2M seen at 64x64 takes 586 instead of 98).
 constexpr int ROW_WIN = 15;
 constexpr int ROW_POINTS = 640;
 constexpr int ROW_POINTS_KNP = 6400;
