@@ -9,6 +9,7 @@ import torch
 from paper_2404_14044_amd import hashpoint as hp
 from paper_2404_14044_amd import scenes
 
+from hp_timing import times_in_turn
 from test_gpu_small_launches import LARGE, SIZES, _check_sizes
 
 pytestmark = pytest.mark.gpu
@@ -32,16 +33,7 @@ def test_time_of_one_bucket_does_not_grow_with_its_square():
         xy = (np.array([[7.5, 4.5]]) + rng.uniform(-0.3, 0.3, (n, 2)) - [cam.cx, cam.cy]) / cam.fx * z[:, None]
         xyz = torch.from_numpy(np.concatenate([xy, z[:, None]], 1).astype(np.float32)).cuda()
         ws = torch.empty(hp.table_workspace(n, [cam], p), dtype=torch.uint8, device="cuda")
-        hp.build_table(xyz, [cam], p, ws=ws)
-        best = float("inf")
-        for _ in range(3):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            hp.build_table(xyz, [cam], p, ws=ws)
-            b.record()
-            torch.cuda.synchronize()
-            best = min(best, a.elapsed_time(b))
-        times.append(best)
+        times += times_in_turn([lambda: hp.build_table(xyz, [cam], p, ws=ws)], reps=3, inner=1)
     assert times[1] <= 27 * times[0], times
 
 

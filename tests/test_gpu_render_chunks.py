@@ -1,11 +1,12 @@
 """Rays per render chunk by default: never much slower than chunks of sixteen rays,
 where all rays are alike, and the same results on both sides of each limit."""
-import numpy as np
 import pytest
 import torch
 
 from paper_2404_14044_amd import hashpoint as hp
 from paper_2404_14044_amd import scenes
+
+from hp_timing import times_in_turn
 
 pytestmark = pytest.mark.gpu
 
@@ -54,16 +55,7 @@ def test_results_on_both_sides_of_the_limits(R, S, prec):
 def test_time_of_full_rays(side, prec, S):
     """Chunks of four rays took up to 1.2 times as long as chunks of sixteen from
     256 x 256 rays of 8 samples on (1.3 in a room, whose neighbours are cached)."""
-    run, times = _setup(side * side, S), {}
-    for rays in (0, 16):
-        times[rays] = float("inf")
-        for _ in range(8):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            for _ in range(6):
-                run(rays, prec)
-            b.record()
-            torch.cuda.synchronize()
-            times[rays] = min(times[rays], a.elapsed_time(b) / 6e-3)
+    run = _setup(side * side, S)
+    times = times_in_turn([lambda: run(0, prec), lambda: run(16, prec)])
     print(side, prec, S, times)
-    assert times[0] <= 1.1 * times[16], times
+    assert times[0] <= 1.1 * times[1], times

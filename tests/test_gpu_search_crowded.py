@@ -8,6 +8,7 @@ import torch
 from paper_2404_14044_amd import hashpoint as hp
 from paper_2404_14044_amd import scenes
 
+from hp_timing import times_in_turn
 from test_gpu_search_groups import _check, _check_knp, _ray_points, _scene
 
 pytestmark = pytest.mark.gpu
@@ -32,18 +33,13 @@ def test_time_of_rays_searched_together(op, per_pixel, bound):
     p = scenes.default_params(0.8 * 2.0 / cam.fx, 1.0, 5.0, K=8, S=16)
     colors = torch.rand(n, 3, generator=gen, device="cuda")
     tab = hp.build_table(xyz, [cam], p)
-    times = []
+    runs = []
     for chunk in (1, 4):
-        q, best = p.replace(search_chunk=chunk), float("inf")
+        q = p.replace(search_chunk=chunk)
         out = hp.alloc_samples(tab.n_rays, q, xyz.device)
-        for _ in range(6):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            hp.search_sample(tab, q, out=out) if op == "search" else hp.knp_blend(tab, q, 8, colors)
-            b.record()
-            torch.cuda.synchronize()
-            best = min(best, a.elapsed_time(b))
-        times.append(best)
+        runs.append((lambda q=q, out=out: hp.search_sample(tab, q, out=out)) if op == "search" else
+                    (lambda q=q: hp.knp_blend(tab, q, 8, colors)))
+    times = times_in_turn(runs)
     print(op, times)
     assert times[1] <= bound * times[0], times
 
