@@ -42,7 +42,7 @@
 // memory (object view, 640k rays, 1M points: 1.6 TB/s).  One ray at a time,
 // with sorted lists kept by merging and four lanes to a candidate, took 309M
 // vector and 123M scalar instructions and 0.509 ms there; this way it takes
-// 157M, 63M and 0.340 ms (room view, 762k rays, 5M points: 2.82 and 1.32 ms).
+// 157M, 63M and 0.346 ms (room view, 762k rays, 5M points: 2.82 and 1.32 ms).
 #pragma once
 #include "hp_device.hpp"
 
@@ -701,7 +701,9 @@ __device__ __forceinline__ void for_each_group_banded(RayGeom *rs, int *take, Gr
     const uint32_t mine = slot < my_chunks ? (my_chunks - slot + n_slots - 1) / n_slots : 0;
     const uint32_t most = MAXG == 1 && NW == 1 && chunk < 4 ? RS_CAP / chunk : 4;
     for (uint32_t at = 0;;) {
-        uint32_t per = most;
+        // (no chunk past the workgroup's last: sixteen of them ahead, in a grid as
+        // large as a launch may have, would pass 2^32)
+        uint32_t per = MAXG == 1 ? min(most, mine - at) : most;
         const int l = phase_lane_id();
         if constexpr (NW > 1) {
             per = min(max((mine - at) / (2 * NW), 1u), most);

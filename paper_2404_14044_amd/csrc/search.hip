@@ -163,7 +163,7 @@ k_search_sample(SearchCtx, SampleOut)
 
 // Bound by the latency of short chains (bisections in the LDS, gathers of a slab's
 // points), so five waves per SIMD with lists of up to 8, though those of 5 to 8
-// spill 20 registers for it (200 positions, us, four / five waves: room of 500k points
+// spill some 15 registers for it (200 positions, us, four / five waves: room of 500k points
 // 900x900 6356 / 5973, plane of 5k 1371 / 1261, object cloud of 1M 1921 / 2028).
 template <int KT>
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(KT <= 8 ? 5 : KT <= 16 ? 4 : 2, 8)))
